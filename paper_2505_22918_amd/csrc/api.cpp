@@ -129,6 +129,7 @@ rt::AttnArgs base_args(const void* q, const void* k, const void* v, const rt_dim
     a.o = static_cast<uint16_t*>(o);
     a.row_max = row_max;
     a.row_sum = row_sum;
+    a.stat_stride = 1;
     a.T = d.T;
     a.n_blk = (int32_t)ceil_div(d.T, block);
     const int64_t items = (int64_t)d.B * d.H * a.n_blk;

@@ -1,7 +1,8 @@
 // Block-sparse / dense softmax attention with row statistics and the fused
 // Re-ttention reshape epilogue, for gfx950 (CDNA4).
 //
-//   rt_attn_full            Eq.1 with the Eq.4 denominator, every key block
+//   rt_attn_full            Eq.1 with the Eq.4 denominator, every key block (short walks;
+//                           attn_dense.hip holds the others)
 //   rt_attn_sparse          Eq.5, the kept key blocks of a block CSR
 //   rt_attn_sparse_reshape  Eq.5, then Eq.9 (rho, ramped) and Eq.10 (residual)
 //
@@ -54,128 +55,11 @@
 
 #include <type_traits>
 
+#include "attn_common.h"
 #include "kernels.h"
 
 namespace rt {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef const __attribute__((address_space(4))) int32_t* csr_ptr;
-typedef __attribute__((address_space(3))) unsigned char lds_u8;
-typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
-typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
-
-constexpr float kJump = 18446744073709551616.0f;  // 2^64: stale-max limit on a probability
-constexpr int kOob = 0x40000000;                   // buffer offset past every record: reads zero
-
-// Geometry of one 32-key chunk of K or V in LDS.
-template <int D>
-struct Geo;
-template <>
-struct Geo<64> {
-    static constexpr int DK = 64;      // Q K^T contraction width (multiple of 16)
-    static constexpr int DV = 64;      // rows of O^T (multiple of 32)
-    static constexpr int SLOTS = 8;    // 16-byte slots per row
-    static constexpr bool SWZ = true;  // XOR-swizzle slots by row
-};
-template <>
-struct Geo<72> {
-    static constexpr int DK = 80;
-    static constexpr int DV = 96;
-    static constexpr int SLOTS = 9;
-    static constexpr bool SWZ = false;
-};
-
-// K rows: 8 consecutive rows read the same slot -> XOR with r & 7.
-template <int D>
-__device__ __forceinline__ int kswz(int r) {
-    return Geo<D>::SWZ ? (r & 7) : 0;
-}
-// V rows: a transpose read covers 4 consecutive rows and, per row, the two
-// slots s and s ^ 2 -> XOR with {0, 1, 4, 5}[r & 3] keeps the 8 (row, slot)
-// pairs of a half-wave on distinct banks.
-template <int D>
-__device__ __forceinline__ int vswz(int r) {
-    return Geo<D>::SWZ ? (((r & 2) << 1) | (r & 1)) : 0;
-}
-
-__device__ __forceinline__ float pair_max(float x) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-__device__ __forceinline__ float pair_sum(float x) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-__device__ __forceinline__ float lo_f(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float hi_f(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    const bf16x2 v = {(__bf16)a, (__bf16)b};
-    return __builtin_bit_cast(uint32_t, v);
-}
-
-// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding:
-// vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] at [15:14]).
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
-// 16 bytes per lane from buffer `rsrc` at byte offset `voff` into LDS at
-// m0 + 16 * lane (buffer_load_dwordx4 ... lds).  m0 is reserved by the compiler
-// (never allocated) and is set before every use; this is sound only while the
-// compiled code keeps nothing else in m0, which the tests check on the
-// assembly of every build.  Issued from inline assembly so
-// the compiler neither orders these loads against LDS reads of other stages nor
-// waits for them; the kernel waits on the vector-memory counter itself.
-__device__ __forceinline__ void dma16(uint32_t lds_addr, int voff, i32x4 rsrc) {
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "buffer_load_dwordx4 %1, %2, 0 offen lds"
-        :
-        : "s"(lds_addr), "v"(voff), "s"(rsrc)
-        : "memory");
-}
-
-// Four such loads at byte offsets voff + 1024 n into LDS m0 + 1024 n + 16 * lane,
-// n = 0..3: the instruction offset moves both the source and the LDS destination.
-__device__ __forceinline__ void dma16x4(uint32_t lds_addr, int voff, i32x4 rsrc) {
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "buffer_load_dwordx4 %1, %2, 0 offen lds\n\t"
-        "buffer_load_dwordx4 %1, %2, 0 offen offset:1024 lds\n\t"
-        "buffer_load_dwordx4 %1, %2, 0 offen offset:2048 lds\n\t"
-        "buffer_load_dwordx4 %1, %2, 0 offen offset:3072 lds"
-        :
-        : "s"(lds_addr), "v"(voff), "s"(rsrc)
-        : "memory");
-}
-
-// 16 bytes per lane from buffer `rsrc` at byte offset `voff` into registers.
-// The data lands later: the caller waits on the vector-memory counter and
-// then passes the value through settle() before reading it.
-__device__ __forceinline__ u32x4 vload16(int voff, i32x4 rsrc) {
-    u32x4 v;
-    asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen" : "=&v"(v) : "v"(voff), "s"(rsrc) : "memory");
-    return v;
-}
-__device__ __forceinline__ void settle(u32x4& v) { asm volatile("" : "+v"(v)); }
-
-__device__ __forceinline__ i32x4 buffer_rsrc(const void* base, int bytes) {
-    const uint64_t p = (uint64_t)(uintptr_t)base;
-    return i32x4{(int)(uint32_t)p, (int)((uint32_t)(p >> 32) & 0xffffu), bytes, 0x00020000};
-}
 
 template <int D, int BS>
 constexpr int kWaves = (D == 72 && BS == 64) ? 1 : 2;
@@ -904,7 +788,7 @@ void attn_fwd(AttnArgs a) {
         // output is added to the residual unscaled
         if (RESHAPE && a.rho) factor *= fminf(1.0f, rho_r[qt] + a.rho_delta);
         if (STATS && hi == 0 && row < T) {
-            const size_t si = (size_t)bh * T + row;
+            const size_t si = ((size_t)bh * T + row) * a.stat_stride;
             if (a.row_max) a.row_max[si] = m_top[qt] * a.scale_nat;
             if (a.row_sum) a.row_sum[si] = l_tot * __builtin_amdgcn_exp2f((m_run[qt] - m_top[qt]) * c2);
         }
@@ -960,7 +844,62 @@ hipError_t launch_db(const AttnArgs& a, AttnMode mode, hipStream_t stream) {
 
 }  // namespace
 
+namespace {
+
+// The same walk over query blocks of 32 rows (dense: any block gives the same keys
+// in the same order).
+AttnArgs in_rows_of_32(AttnArgs a) {
+    const int64_t n_bh = a.n_items / a.n_blk;
+    a.n_blk = (a.T + 31) / 32;
+    a.n_items = (int32_t)(n_bh * a.n_blk);
+    a.per_xcd = (a.n_items + 7) / 8;
+    return a;
+}
+
+// Dense attention.  Up to 1024 waves of 32 rows (one per SIMD of the chip) a chunk's
+// latency bounds the call, and the shortest walk wins: waves of 32 rows with a
+// ring each (D = 64, two heads of 4096 tokens: 43 us, against 66 in rows of 64 and 74 with
+// a shared ring; D = 72: 70, 110, 84).  Above, the matrix and vector units do: waves
+// of 64 rows over a shared ring (D = 72, 32 heads of 4096: 157 us, against 266 and 228).
+// In between, a 64-wide head without statistics keeps the private ring while there is at
+// most one wave of 64 rows per SIMD (8 heads of 8192: 145 us, 150 shared; with
+// statistics 162 and 148).
+hipError_t launch_dense(const AttnArgs& a, int D, int block, hipStream_t stream) {
+    const int64_t n_bh = a.n_items / a.n_blk;
+    if (n_bh * ((a.T + 31) / 32) <= 1024)
+        return D == 64 ? launch_db<64, 32>(in_rows_of_32(a), kAttn, stream)
+                       : launch_db<72, 32>(in_rows_of_32(a), kAttn, stream);
+    if (D == 64 && block == 64 && a.n_items <= 1024 && !a.row_max && !a.row_sum)
+        return launch_db<64, 64>(a, kAttn, stream);
+    return launch_attention_dense(a, D, false, stream);
+}
+
+// Whether a caching step over 64-token blocks runs as the sparse walk and then the dense
+// walk over the dropped keys.  The dense walk spends its time on every block, so the
+// two cost 1 + (kept share) dense walks: worth it while that stays below its gain
+// over the single kernel (1.16x at D = 64, 1.5x at D = 72, CogVideoX and PixArt-Sigma-2K
+// shapes).  Short walks do not pay for the second launch (D = 64: 1024 tokens
+// 31 us against 28, 2048 tokens 51 and 51, 4096 tokens 90 and 97; D = 72: 256 tokens 20 and
+// 15, 1024 tokens 36 and 39).
+bool cache_in_two(const AttnArgs& a, int D) {
+    if (a.T < (D == 64 ? 2048 : 1024)) return false;
+    const double blocks = (double)a.n_masks * a.n_blk * a.n_blk;
+    return a.nnz <= blocks / (D == 64 ? 8 : 3);
+}
+
+}  // namespace
+
 hipError_t launch_attention(const AttnArgs& a, int D, int block, AttnMode mode, hipStream_t stream) {
+    if (mode == kAttn && a.dense) return launch_dense(a, D, block, stream);
+    if (mode == kAttnCache && block == 64 && !a.postmask && cache_in_two(a, D)) {
+        AttnArgs s = a;  // O_s to o, the kept keys' statistics to the residual rows
+        s.row_max = reinterpret_cast<float*>(a.resid_out);
+        s.row_sum = s.row_max + 1;
+        s.stat_stride = D / 2;
+        s.scale_nat = 1.0f;
+        const hipError_t e = D == 64 ? launch_db<64, 64>(s, kAttn, stream) : launch_db<72, 64>(s, kAttn, stream);
+        return e != hipSuccess ? e : launch_attention_dense(a, D, true, stream);
+    }
     if (D == 64) return block == 64 ? launch_db<64, 64>(a, mode, stream) : launch_db<64, 32>(a, mode, stream);
     return block == 64 ? launch_db<72, 64>(a, mode, stream) : launch_db<72, 32>(a, mode, stream);
 }
