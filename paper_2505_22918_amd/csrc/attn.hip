@@ -6,6 +6,10 @@
 //   rt_attn_sparse          Eq.5, the kept key blocks of a block CSR
 //   rt_attn_sparse_reshape  Eq.5, then Eq.9 (rho, ramped) and Eq.10 (residual)
 //
+// Masks of 64-token blocks run attn_rows64 below: one wavefront per 64 query rows,
+// the two-tile walk of attn_tiles.h.  Masks of 32-token blocks, and caching steps
+// that are not worth two kernels, run attn_fwd, which this comment describes.
+//
 // One workgroup is one wavefront that owns one query block (32 or 64 rows) of
 // one (batch, head) and walks the key blocks of its CSR row in 32-key chunks:
 //
@@ -55,7 +59,7 @@
 
 #include <type_traits>
 
-#include "attn_common.h"
+#include "attn_tiles.h"
 #include "kernels.h"
 
 namespace rt {
@@ -821,6 +825,292 @@ void attn_fwd(AttnArgs a) {
     }
 }
 
+// Sparse (or dense) attention in rows of 64 queries: one workgroup is one wavefront that
+// walks the key blocks of its CSR row in 32-key chunks (attn_tiles.h).
+//
+// K and V chunks move from HBM/L2 into two-stage LDS rings with buffer_load ... lds (no
+// staging registers).  A step reads all of K(t+1) and V(t) into operand registers, so both
+// stages are free at its end and take K(t+3) and V(t+2): two steps of lead with 16 KB
+// of LDS a wave at D = 64 and 20 KB at D = 72, eight waves per CU.  In the fused
+// reshape the K loads of the two chunks past the row bring the block's residual rows
+// instead, which the epilogue reads from LDS.
+//
+// Bound by power and by the memory streams at once: at the CogVideoX shape, without the
+// output stores, the residual loads and with K and V from one hot region the fused
+// call takes 201, 216 and 211 us instead of 226, with all three 173.  Delaying
+// half of the first waves, wave priorities and an earlier K(0) change nothing.
+// Measured, fused call, before -> now: PixArt-Sigma-2K (32 heads, 16384 tokens, D = 72)
+// 164 -> 125 us (two waves per SIMD instead of one: 131; rows stored from LDS: 125),
+// PixArt-Sigma-1024 22.2 -> 18.1 us, CogVideoX (60 heads, 17776 tokens, D = 64)
+// 230 -> 223 us (the first step forms no P V and the last no scores: 4 % fewer MFMAs).
+template <int D, bool RESHAPE, bool STATS>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_rows64(AttnArgs a) {
+    using G = Geo<D>;
+    constexpr int BS = 64;
+    constexpr int ROWB = G::SLOTS * 16;      // LDS bytes per K / V row (= 2 * D)
+    constexpr int HALF = 32 * ROWB;          // one 32-key chunk, one ring stage
+    constexpr int NDMA = (HALF + 1023) / 1024;  // DMA instructions per chunk and tensor
+    constexpr bool TAIL = D == 72;
+    // K stages at 0 and HALF, V stages at 2 HALF and 3 HALF, zeros for the tails' operands
+    constexpr int ZERO = 4 * HALF;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[ZERO + (TAIL ? 8 * ROWB + 16 : 0)];
+    lds_u8* const lds = (lds_u8*)smem;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+    const int lane = threadIdx.x;
+    const int l32 = lane & 31;
+    const int hi = lane >> 5;
+
+    // XCD-aware order: hardware workgroup g runs on XCD g % 8; give each XCD a
+    // contiguous run of (head, query block) items so a head's K/V stays in one L2.
+    const int g = blockIdx.x;
+    const int item = (g & 7) * a.per_xcd + (g >> 3);
+    if (item >= a.n_items) return;
+    const int bh = item / a.n_blk;
+    const int qb = item - bh * a.n_blk;
+    const int T = a.T;
+    const size_t head_off = (size_t)bh * (size_t)T * D;
+    const int row0 = qb * BS;  // first query row of the block
+    const int nrow = (T - row0) < BS ? (T - row0) : BS;
+
+    Tiles<D, STATS, STATS, ZERO> t;
+    t.init(lds, lane, T, a.scale_log2);
+    // Q first, so that its HBM latency runs under the reads of the CSR row below
+    t.load_q(a.q + head_off + (size_t)row0 * D, nrow);
+    float rho_r[2];
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+        const int row = row0 + qt * 32 + l32;
+        rho_r[qt] = (RESHAPE && a.rho && row < T) ? a.rho[(size_t)bh * T + row] : 0.f;
+    }
+    if (TAIL && lane < 2) *(lds_u32x4*)(lds + ZERO + lane * 8 * ROWB) = u32x4{};
+
+    // ---- kept key blocks of this query block ----------------------------------------
+    int e_beg, e_end;
+    if (a.dense) {
+        e_beg = 0;
+        e_end = a.n_blk;
+    } else {
+        // the mask of this (batch, head): shared, per head, or per (batch, head)
+        const int mid = a.n_masks <= 1 ? 0 : (a.n_masks == a.heads ? bh % a.heads : bh);
+        const csr_ptr rp = (csr_ptr)a.row_ptr + (size_t)mid * (a.n_blk + 1);
+        e_beg = rp[qb];
+        e_end = rp[qb + 1];
+        e_beg = e_beg < 0 ? 0 : (e_beg > a.nnz ? a.nnz : e_beg);
+        e_end = e_end < e_beg ? e_beg : (e_end > a.nnz ? a.nnz : e_end);
+    }
+    // Chunk i is kept entry i / 2, 32-key half i % 2.  The first 64 column indices live in
+    // one VGPR (lane j holds entry e_beg + j); longer rows read the rest with loads.
+    const int n = (e_end - e_beg) * 2;
+    int cols = -1;
+    if (!a.dense && lane < e_end - e_beg) cols = a.col_idx[e_beg + lane];
+    // A chunk is addressed by the byte offset of its first key row in the head's K (or V)
+    // buffer, or kOob for a chunk that holds no key (past the row, past T, an entry
+    // outside [0, n_blk)): its loads read zeros and its scores are masked.
+    auto offset = [&](int kb, int i) {
+        const int base = kb * BS + 32 * (i & 1);
+        return (i < n && kb >= 0 && kb < a.n_blk && base < T) ? base * (D * 2) : kOob;
+    };
+    // The first chunks' entries come by scalar loads: vector loads return in order, and
+    // `cols` behind Q, whose HBM latency the first K and V loads are not to wait for.
+    int kb0 = 0, kb1 = 1;
+    if (!a.dense && n > 0) {
+        kb0 = ((csr_ptr)a.col_idx)[e_beg];
+        kb1 = n > 2 ? ((csr_ptr)a.col_idx)[e_beg + 1] : -1;
+    }
+    int o0 = offset(kb0, 0), o1 = offset(kb0, 1), o2 = offset(kb1, 2);  // chunks t, t + 1, t + 2
+    // The offsets of 64 consecutive chunks tb .. tb+63 sit in one VGPR, refilled every 64
+    // steps.
+    int tab = kOob, tb = 0;
+    auto fill_tab = [&](int c0) {
+        tb = c0;
+        const int i = c0 + lane;
+        const int j = i >> 1;
+        int kb = j;
+        if (!a.dense) {
+            const int last = (c0 + 63 < n ? c0 + 63 : n - 1) >> 1;
+            if (last < 64) {  // every entry this table needs sits in `cols`
+                kb = __builtin_amdgcn_ds_bpermute((j & 63) << 2, cols);
+            } else {  // a row of more than 64 entries: read them (rare)
+                const int e = i < n ? e_beg + j : 0;
+                kb = a.col_idx[e];
+            }
+        }
+        tab = offset(kb, i);
+        asm volatile("" : "+v"(tab));
+    };
+
+    // Lane fills 16-byte slot m * 64 + lane of a chunk from row r = slot / SLOTS, head-dim
+    // chunk (slot % SLOTS) ^ swizzle(r): 8 rows an instruction when swizzled, contiguous
+    // rows otherwise.
+    int kdma = lane * 16, vdma = lane * 16;
+    if (G::SWZ) {
+        const int r = lane >> 3, s = lane & 7;
+        kdma = r * ROWB + ((s ^ kswz<D>(r)) * 16);
+        vdma = r * ROWB + ((s ^ vswz<D>(r)) * 16);
+    }
+    auto dma = [&](const i32x4& rs, int off, int dst) {
+        const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds0 + dst);
+        dma16x4(m0, off, rs);
+        if (TAIL && lane < 32) dma16(m0 + 4096, off + 4096, rs);
+    };
+    const i32x4 k_rs = buffer_rsrc(a.k + head_off, T * D * 2);
+    const i32x4 v_rs = buffer_rsrc(a.v + head_off, T * D * 2);
+    const i32x4 r_rs = RESHAPE ? buffer_rsrc(a.resid + head_off + (size_t)row0 * D, nrow * D * 2) : k_rs;
+    // K load of chunk c; past the row (c = n, n + 1) the residual rows 32 (c - n) ..
+    auto issue_k = [&](int c, int boff, int dst) {
+        if (RESHAPE && c >= n) {
+            dma(r_rs, kdma + (c - n) * HALF, dst);
+        } else {
+            dma(k_rs, kdma + boff, dst);
+        }
+    };
+    // every LDS read so far has returned: its stage may be overwritten
+    auto reads_done = [&]() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+
+    issue_k(0, o0, 0);
+    issue_k(1, o1, HALF);
+    dma(v_rs, vdma + o0, 2 * HALF);
+    wait_vm<2 * NDMA>();  // K(0) has landed, and what was issued before it
+    // no wait of the compiler's in the walk
+    asm volatile("" : "+v"(cols), "+v"(rho_r[0]), "+v"(rho_r[1])::"memory");
+    t.settle_q();
+    if (n > 0) {
+        t.first_chunk(0, o0);
+        fill_tab(0);
+        t.first_max(0, o0);
+        reads_done();
+        issue_k(2, o2, 0);
+        dma(v_rs, vdma + o1, 3 * HALF);
+    }
+
+    // Step i: K(i+1) and V(i) have landed when the loads of step i - 1 are the only ones
+    // in flight.  Every step but the last issues the same number of them.  The first
+    // has both tiles' scores and nothing pending, the last forms no scores.
+    int ks = HALF, vs = 2 * HALF;  // stages of K(i+1) and V(i)
+    auto landed = [&]() {
+        wait_vm<2 * NDMA>();
+        asm volatile("" ::: "memory");
+    };
+    auto refill = [&](int i) {
+        reads_done();
+        if (i + 3 - tb >= 64) fill_tab(i + 3);
+        const int o3 = __builtin_amdgcn_readlane(tab, i + 3 - tb);
+        issue_k(i + 3, o3, ks);
+        dma(v_rs, vdma + o2, vs);
+        o0 = o1;
+        o1 = o2;
+        o2 = o3;
+        ks = HALF - ks;
+        vs = 5 * HALF - vs;
+    };
+    if (n > 0) {  // an even number: two chunks to a block
+        landed();
+        t.template phase<0, false, false>(true, o0, ks, vs);
+        t.template phase<1>(true, o1, ks, vs);
+        refill(0);
+        for (int i = 1; i + 1 < n; ++i) {
+            landed();
+            t.template phase<0>(true, o0, ks, vs);
+            t.template phase<1>(true, o1, ks, vs);
+            refill(i);
+        }
+        landed();
+        t.template phase<0>(true, o0, ks, vs);
+        t.template phase<1, false, true>(true, 0, ks, vs);
+    }
+    t.pv1();
+    wait_vm<0>();  // the residual rows, and nothing may land in LDS after the wave has ended
+    asm volatile("" ::: "memory");
+
+    // ---- epilogue: O = factor * acc (+ R), through the V stages to memory ---------------
+    // A lane holds 16 consecutive head dims of a row, so stores straight from registers
+    // would write 16-byte pieces of 32 rows each; from LDS an instruction writes
+    // 1024 contiguous bytes.  Rows in LDS as K rows (swizzled or contiguous).
+    constexpr int OUT = 2 * HALF;
+    float factor[2];
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+        const int row = row0 + qt * 32 + l32;
+        const float l_tot = pair_sum(t.l_run[qt]);
+        factor[qt] = 1.0f / l_tot;
+        // without a ratio (the ablation with the reshape removed) the sparse
+        // output is added to the residual unscaled
+        if (RESHAPE && a.rho) factor[qt] *= fminf(1.0f, rho_r[qt] + a.rho_delta);
+        if (STATS) t.m_top[qt] = pair_max(t.m_top[qt]);
+        if (STATS && hi == 0 && row < T) {
+            const size_t si = ((size_t)bh * T + row) * a.stat_stride;
+            if (a.row_max) a.row_max[si] = t.m_top[qt] * a.scale_nat;
+            if (a.row_sum) a.row_sum[si] = l_tot * __builtin_amdgcn_exp2f((t.m_run[qt] - t.m_top[qt]) * a.scale_log2);
+        }
+        const lds_u8* Rs = lds + ((n + qt) & 1) * HALF;  // residual rows: the K stage of chunk n + qt
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int ch = 4 * dt + 2 * hi + u;  // head dims 8ch .. 8ch+7
+                const int at = l32 * ROWB + ((ch ^ kswz<D>(l32)) * 16);
+                float y[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[e] = t.oacc[qt][dt][8 * u + e] * factor[qt];
+                if (RESHAPE) {
+                    const u32x4 r4 = *(const lds_u32x4*)(Rs + at);
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        y[2 * w] += lo_f(r4[w]);
+                        y[2 * w + 1] += hi_f(r4[w]);
+                    }
+                }
+                *(lds_u32x4*)(lds + OUT + qt * HALF + at) = u32x4{pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]),
+                                                                  pack_bf16(y[4], y[5]), pack_bf16(y[6], y[7])};
+            }
+        }
+    }
+    if (TAIL) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float f = t.tail_bcast(factor[0], factor[1], h);
+            // row of tile hi, dims 64 + 4 (lane / 16 % 2) ..
+            const int at = (16 * h + (lane & 15)) * ROWB + 128 + 8 * ((lane >> 4) & 1);
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = t.tacc[h][e] * f;
+            if (RESHAPE) {
+                const lds_u8* Rs = lds + ((n + hi) & 1) * HALF + at;
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    const uint32_t r = *(const lds_u32*)(Rs + 4 * w);
+                    y[2 * w] += lo_f(r);
+                    y[2 * w + 1] += hi_f(r);
+                }
+            }
+            lds_u32* dst = (lds_u32*)(lds + OUT + hi * HALF + at);
+            dst[0] = pack_bf16(y[0], y[1]);
+            dst[1] = pack_bf16(y[2], y[3]);
+        }
+    }
+    // 16-byte slot s of the block's contiguous output rows
+    uint16_t* const out = a.o + head_off + (size_t)row0 * D;
+#pragma unroll
+    for (int m = 0; m < G::SLOTS; ++m) {
+        const int s = m * 64 + lane;
+        const int r = s / G::SLOTS, c = s - r * G::SLOTS;
+        if (r < nrow) *reinterpret_cast<u32x4*>(out + 8 * s) = *(const lds_u32x4*)(lds + OUT + r * ROWB + ((c ^ kswz<D>(r)) * 16));
+    }
+}
+
+template <int D, bool RESHAPE, bool STATS>
+hipError_t launch_rows64(const AttnArgs& a, hipStream_t stream) {
+    hipLaunchKernelGGL((attn_rows64<D, RESHAPE, STATS>), dim3(8 * a.per_xcd), dim3(64), 0, stream, a);
+    return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_rows64(const AttnArgs& a, AttnMode mode, hipStream_t stream) {
+    const bool stats = a.row_max != nullptr || a.row_sum != nullptr;
+    if (mode == kAttnReshape) return stats ? launch_rows64<D, true, true>(a, stream) : launch_rows64<D, true, false>(a, stream);
+    return stats ? launch_rows64<D, false, true>(a, stream) : launch_rows64<D, false, false>(a, stream);
+}
+
 template <int D, int BS, bool RESHAPE, bool STATS, bool CACHE>
 hipError_t launch_one(const AttnArgs& a, hipStream_t stream) {
     dim3 grid(8 * a.per_xcd), block(64);
@@ -831,14 +1121,14 @@ hipError_t launch_one(const AttnArgs& a, hipStream_t stream) {
 template <int D, int BS>
 hipError_t launch_db(const AttnArgs& a, AttnMode mode, hipStream_t stream) {
     const bool stats = a.row_max != nullptr || a.row_sum != nullptr;
-    switch (mode) {
-        case kAttnReshape:
-            return stats ? launch_one<D, BS, true, true, false>(a, stream) : launch_one<D, BS, true, false, false>(a, stream);
-        case kAttnCache:
-            return stats ? launch_one<D, BS, false, true, true>(a, stream) : launch_one<D, BS, false, false, true>(a, stream);
-        default:
-            return stats ? launch_one<D, BS, false, true, false>(a, stream)
-                         : launch_one<D, BS, false, false, false>(a, stream);
+    if (mode == kAttnCache)
+        return stats ? launch_one<D, BS, false, true, true>(a, stream) : launch_one<D, BS, false, false, true>(a, stream);
+    if constexpr (BS == 64) {
+        return launch_rows64<D>(a, mode, stream);
+    } else if (mode == kAttnReshape) {
+        return stats ? launch_one<D, BS, true, true, false>(a, stream) : launch_one<D, BS, true, false, false>(a, stream);
+    } else {
+        return stats ? launch_one<D, BS, false, true, false>(a, stream) : launch_one<D, BS, false, false, false>(a, stream);
     }
 }
 

@@ -19,6 +19,7 @@ typedef __attribute__((address_space(3))) unsigned char lds_u8;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
 
 constexpr float kJump = 18446744073709551616.0f;  // 2^64: stale-max limit on a probability
 constexpr int kOob = 0x40000000;                   // buffer offset past every record: reads zero
