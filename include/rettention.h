@@ -156,8 +156,8 @@ rt_status rt_index_build(const rt_pattern* pattern, int32_t T, int32_t block, in
  *   score(qb, kb) = sum_d Qsum_qb[d] * Kmean_kb[d]
  * Qsum: the fp32 sum of qb's rows, one addition per row in ascending order;
  * Kmean: kb's rows summed the same way, divided by its token count; the dot
- * product accumulates in fp32 over ascending d, product and sum each rounded
- * (no fused multiply-add).  qb keeps itself (Eq.5 needs a non-empty kept set)
+ * product accumulates in fp32 over ascending d by fused multiply-adds, one
+ * rounding a term.  qb keeps itself (Eq.5 needs a non-empty kept set)
  * and the keep - 1 best other blocks (higher score first, ties to the lower
  * index; a NaN score ranks as -inf, after every other score), stored
  * ascending, so every row holds exactly

@@ -9,8 +9,8 @@
 //   score(qb, kb) = sum_d Qsum_qb[d] * Kmean_kb[d]
 // with Qsum the fp32 sum of qb's rows (one addition per row, ascending), Kmean
 // the fp32 sum of kb's rows (same order) divided by its token count, and the
-// dot product accumulated in fp32 over ascending d with the product and the sum
-// rounded separately.  qb keeps itself (Eq.5 needs a non-empty kept set) and
+// dot product accumulated in fp32 over ascending d by fused multiply-adds (one
+// rounding a term).  qb keeps itself (Eq.5 needs a non-empty kept set) and
 // the keep - 1 best other blocks (higher score first, ties to the lower index,
 // a NaN score ranked last); rows are stored ascending.  Every fp32 operation is
 // fixed, so the choice is reproducible bit for bit.
@@ -19,22 +19,31 @@
 //                  rows are staged in LDS with 16-byte loads, then lane d < D
 //                  sums Q column d over the rows in ascending order and lane
 //                  128 + d does the same for K and divides by the token count.
-//                  Writes qsum and kmean [B*H][n_blk][D].
-//   select_kernel  one workgroup per (batch, head) and `rows` consecutive
-//                  query blocks (8, halved until the scores fit 32 KB of
-//                  LDS: 2 at 4096 blocks): the key means pass through LDS in chunks of
-//                  kSelChunk blocks (one 16-byte load per lane and round), each
-//                  lane scoring one (query block, key block) pair of the chunk;
-//                  then one wave per row: a radix selection of the keep - 1
-//                  best other blocks (independent of keep: four histogram
-//                  passes over the candidates) and the kept blocks in
+//                  Writes qsum [B*H][n_blk][D] and, per 64-block tile, kmean as
+//                  [D / 4][blocks of the tile][4], the order a wave reads it in.
+//                  Bound by HBM: CogVideoX shape 43 us for 273 MB.
+//   select_kernel  one workgroup per (batch, head) and a few query blocks, a wave per
+//                  tile of 64 key blocks (up to 8 waves) and two rows per wave while the
+//                  scores fit 40 KB of LDS.  A lane keeps its key block's mean in
+//                  registers and takes the query values from scalar registers, so
+//                  that a term of a score is one vector instruction and no LDS read.
+//                  Then one wave per row selects: up to 512 blocks with the keys in
+//                  registers, the threshold found bit by bit with ballots (ends when
+//                  exactly as many keys are above it as are to be kept); longer rows by
+//                  four radix passes over LDS histograms, whose cost per bit does
+//                  not grow with the registers.  The kept blocks go out in
 //                  ascending order at the row's closed-form offset (every row
 //                  keeps exactly min(keep, n_blk)).
+// Bound by the latency of the scalar loads and the L2 reads of the key means.  CogVideoX
+// shape (60 heads, 278 blocks, keep 9), before -> now: selection 65 -> 35 us (10 of them
+// the selection proper), the build 102-109 -> 85 us; one and four rows per wave 37 and
+// 41 us; key means read row by row instead of by tiles 40 us.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -44,17 +53,16 @@ namespace rt {
 namespace {
 
 constexpr int kPoolThreads = 256;
-constexpr int kSelThreads = 512;
-constexpr int kSelRows = 8;                         // most query blocks per select workgroup
-constexpr int kSelChunk = kSelThreads / kSelRows;  // key blocks per LDS chunk
-constexpr int kSelScoreBytes = 32 << 10;           // LDS for the scores of one workgroup
-static_assert(kSelThreads / 64 >= kSelRows, "one wave per selected row");
+constexpr int kSelWaves = 8;             // most waves of a select workgroup
+constexpr int kSelRegs = 8;              // up to 64 times as many blocks are selected in registers
+constexpr int kSelScoreBytes = 40 << 10; // LDS for the scores of one workgroup
 constexpr int kMaxD = 72;
 constexpr int kPoolRows = 64;                      // largest block
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(4))) float* float_cptr;
 
 __global__ __launch_bounds__(kPoolThreads) void pool_kernel(const uint16_t* __restrict__ q,
                                                             const uint16_t* __restrict__ k, int T, int D,
@@ -85,11 +93,12 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(const uint16_t* __re
     const uint16_t* col = tile[is_q ? 0 : 1] + d;
     float acc = 0.0f;
     for (int r = 0; r < cnt; ++r) acc = __fadd_rn(acc, bf16_to_f32(col[r * D]));
-    const size_t o = ((size_t)bh * n_blk + b) * D + d;
     if (is_q) {
-        qsum[o] = acc;
+        qsum[((size_t)bh * n_blk + b) * D + d] = acc;
     } else {
-        kmean[o] = __fdiv_rn(acc, (float)cnt);
+        const int t0 = b & ~63;
+        const int nt = n_blk - t0 < 64 ? n_blk - t0 : 64;
+        kmean[((size_t)bh * n_blk + t0) * D + ((d >> 2) * nt + (b - t0)) * 4 + (d & 3)] = __fdiv_rn(acc, (float)cnt);
     }
 }
 
@@ -116,159 +125,183 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-__global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __restrict__ qsum,
-                                                             const float* __restrict__ kmean, int D, int n_blk,
-                                                             int keep, int rows, int32_t* __restrict__ row_ptr,
-                                                             int32_t* __restrict__ col_idx) {
-    // scores of the workgroup's rows: rows x n_blk floats of dynamic LDS
+// Scores of the key blocks t0 + lane against `rows` pooled queries, into sc[row][kb].
+template <int D>
+__device__ __forceinline__ void score_tile(const float* __restrict__ qrow, const float* __restrict__ kh, int t0,
+                                           int n_blk, int rows, float* sc, int lane) {
+    float k[D];
+    const int nt = n_blk - t0 < 64 ? n_blk - t0 : 64;
+    const int kb = t0 + lane;
+    const u32x4* src = reinterpret_cast<const u32x4*>(kh + (size_t)t0 * D) + (lane < nt ? lane : nt - 1);
+#pragma unroll
+    for (int i = 0; i < D / 4; ++i) {
+        const u32x4 x = src[i * nt];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) k[4 * i + e] = __uint_as_float(x[e]);
+    }
+    const float_cptr q = (float_cptr)qrow;
+    for (int r = 0; r < rows; r += 2) {  // two rows at a time: two chains of sums
+        const int r1 = r + 1 < rows ? r + 1 : r;
+        float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            s0 = __builtin_fmaf(q[r * D + d], k[d], s0);
+            s1 = __builtin_fmaf(q[r1 * D + d], k[d], s1);
+        }
+        if (kb < n_blk) {
+            sc[r * n_blk + kb] = s0;
+            sc[r1 * n_blk + kb] = s1;
+        }
+    }
+}
+
+// The keep - 1 best blocks other than the diagonal, by the value of their keys: thr, the
+// key of the worst of them, and how many blocks holding exactly thr are kept.
+struct Cut {
+    uint32_t thr;
+    int rem;
+};
+
+// Up to 64 N candidates, key u[i] of block lane + 64 i in registers (0, below every
+// score's key, where there is none): thr bit by bit from the top, counting the keys
+// at or above it by ballots, until exactly `need` are.
+template <int N>
+__device__ __forceinline__ Cut cut_in_registers(const uint32_t (&u)[N], int need) {
+    uint32_t thr = 0;
+    for (uint32_t bit = 0x80000000u; bit; bit >>= 1) {
+        int cnt = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) cnt += __popcll(__ballot(u[i] >= (thr | bit)));
+        if (cnt >= need) thr |= bit;
+        if (cnt == need) break;
+    }
+    int above = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) above += __popcll(__ballot(u[i] > thr));
+    return {thr, need - above};
+}
+
+// Any number of candidates, scores in LDS: radix selection, four passes of 8-bit digits
+// from the top over a wave's histogram.
+__device__ __forceinline__ Cut cut_by_radix(const float* row, int n_blk, int qb, int need, int* hw, int lane) {
+    const int n_round = (n_blk + 63) / 64;
+    uint32_t thr = 0, thr_mask = 0;  // digits of the threshold found so far
+    int rem = need;                   // blocks still to keep at the threshold
+    for (int shift = 24; shift >= 0; shift -= 8) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) hw[4 * lane + j] = 0;
+        wave_lds_sync();
+        for (int i = 0; i < n_round; ++i) {
+            const int c = lane + 64 * i;
+            if (c < n_blk && c != qb) {
+                const uint32_t key = order_key(row[c]);
+                if ((key & thr_mask) == thr) atomicAdd(&hw[(key >> shift) & 255u], 1);
+            }
+        }
+        wave_lds_sync();
+        // lane L holds bins 4L .. 4L+3; S(t) counts the blocks with digit >= t
+        // and the threshold's digit is the t with S(t+1) < rem <= S(t)
+        int h[4], sum = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            h[j] = hw[4 * lane + j];
+            sum += h[j];
+        }
+        int incl = sum;  // inclusive sum over lanes 0 .. lane
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += y;
+        }
+        const int tot = __shfl(incl, 63, 64);
+        int s_t = tot - incl;  // bins above this lane's four
+        int dig = -1, nrem = 0;
+#pragma unroll
+        for (int j = 3; j >= 0; --j) {
+            s_t += h[j];
+            if (h[j] > 0 && s_t >= rem && s_t - h[j] < rem) {
+                dig = 4 * lane + j;
+                nrem = rem - (s_t - h[j]);
+            }
+        }
+        const unsigned long long found = __ballot(dig >= 0);
+        const int src = __builtin_ctzll(found);  // exactly one lane finds it
+        thr |= (uint32_t)__shfl(dig, src, 64) << shift;
+        thr_mask |= 255u << shift;
+        rem = __shfl(nrem, src, 64);
+    }
+    return {thr, rem};
+}
+
+// N: 64-block tiles of a row selected in registers, 0 for any number by radix passes
+template <int D, int N>
+__global__ __launch_bounds__(64 * kSelWaves) void select_kernel(const float* __restrict__ qsum,
+                                                                const float* __restrict__ kmean, int n_blk, int keep,
+                                                                int rows, int32_t* __restrict__ row_ptr,
+                                                                int32_t* __restrict__ col_idx) {
+    // scores of the workgroup's rows: rows x n_blk floats, then (radix) the waves' histograms
     extern __shared__ float sc[];
-    __shared__ __attribute__((aligned(16))) float qv[kSelRows][kMaxD];  // pooled queries of the rows
-    // one chunk of key means, rows padded by four floats so that the 16-byte
-    // reads of 16 lanes (16 consecutive key blocks) cover the 64 banks once
-    __shared__ __attribute__((aligned(16))) float km[kSelChunk * (kMaxD + 4)];
     const int n_grp = (n_blk + rows - 1) / rows;
     const int bh = blockIdx.x / n_grp;
     const int qb0 = (blockIdx.x - bh * n_grp) * rows;
-    const int tid = threadIdx.x;
+    const int n_row = n_blk - qb0 < rows ? n_blk - qb0 : rows;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_wave = blockDim.x >> 6;
     const int kk = keep < n_blk ? keep : n_blk;
-    const int kst = D + 4;  // LDS row stride of km (floats; a multiple of 4)
-    for (int i = tid; i < rows * D; i += kSelThreads) {
-        const int r = i / D, d = i - r * D;
-        qv[r][d] = qb0 + r < n_blk ? qsum[((size_t)bh * n_blk + qb0 + r) * D + d] : 0.0f;
-    }
-    const float* kh = kmean + (size_t)bh * n_blk * D;
-    const int pr = tid / kSelChunk;  // the pair this lane scores: row pr,
-    const int pc = tid - pr * kSelChunk;  // key block c0 + pc
-    // A chunk's nc * D floats are contiguous in HBM: 16-byte pieces i, piece
-    // tid + kSelThreads j in register pf[j].  The next chunk's loads are in
-    // flight while the current one is scored.
-    constexpr int kPieces = (kSelChunk * kMaxD / 4 + kSelThreads - 1) / kSelThreads;
-    u32x4 pf[kPieces];
-    auto load_chunk = [&](int c0) {
-        const int nc = n_blk - c0 < kSelChunk ? n_blk - c0 : kSelChunk;
-        const int n16 = nc * D / 4;
-        const u32x4* src = reinterpret_cast<const u32x4*>(kh + (size_t)c0 * D);
-#pragma unroll
-        for (int j = 0; j < kPieces; ++j) {
-            const int i = tid + kSelThreads * j;
-            if (i < n16) pf[j] = src[i];
-        }
-    };
-    load_chunk(0);
-    for (int c0 = 0; c0 < n_blk; c0 += kSelChunk) {
-        const int nc = n_blk - c0 < kSelChunk ? n_blk - c0 : kSelChunk;
-        __syncthreads();  // the previous chunk's scores are done (and qv is in)
-        const int n16 = nc * D / 4;
-#pragma unroll
-        for (int j = 0; j < kPieces; ++j) {
-            const int i = tid + kSelThreads * j;
-            if (i < n16) {
-                const int e = 4 * i, r = e / D, d = e - r * D;  // D is a multiple of 4
-                *reinterpret_cast<u32x4*>(km + r * kst + d) = pf[j];
-            }
-        }
-        __syncthreads();
-        if (c0 + kSelChunk < n_blk) load_chunk(c0 + kSelChunk);
-        if (pr < rows && pc < nc) {
-            const u32x4* kv = reinterpret_cast<const u32x4*>(km + pc * kst);
-            const u32x4* qq = reinterpret_cast<const u32x4*>(qv[pr]);
-            float s = 0.0f;
-            for (int d4 = 0; d4 < D / 4; ++d4) {
-                const u32x4 a = qq[d4], b = kv[d4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s = __fadd_rn(s, __fmul_rn(__uint_as_float(a[e]), __uint_as_float(b[e])));
-            }
-            sc[pr * n_blk + c0 + pc] = s;
-        }
-    }
-    __syncthreads();
-    // Selection: wave w takes row w.  Candidate block c = lane + 64 i (round
-    // i).  The keep - 1 best blocks other than the diagonal are found by radix
-    // selection on the 32-bit keys: four passes of 8-bit digits, from the top,
-    // narrow the key of the (keep-1)-th best block (the threshold) and how many
-    // blocks holding exactly that key are kept; those go to the lowest indices.
-    // Every block with a larger key is kept.
-    __shared__ int hist[kSelThreads / 64][256];
-    const int lane = tid & 63, w = tid >> 6;
-    const int qb = qb0 + w;
-    if (w >= rows || qb >= n_blk) return;  // no barrier follows
-    const float* row = sc + w * n_blk;
-    int* hw = hist[w];
-    const int n_round = (n_blk + 63) / 64;
     const int need = kk - 1;  // other blocks to keep, < n_blk
-    uint32_t thr = 0, thr_mask = 0;  // digits of the threshold found so far
-    int rem = need;                   // blocks still to keep at the threshold
-    if (need > 0 && need < n_blk - 1) {
-        for (int shift = 24; shift >= 0; shift -= 8) {
+    const float* kh = kmean + (size_t)bh * n_blk * D;
+    const float* qrow = qsum + ((size_t)bh * n_blk + qb0) * D;
+    for (int t = w; t * 64 < n_blk; t += n_wave) score_tile<D>(qrow, kh, t * 64, n_blk, n_row, sc, lane);
+    __syncthreads();
+    // one wave per row
+    for (int r = w; r < n_row; r += n_wave) {
+        const int qb = qb0 + r;
+        const float* row = sc + r * n_blk;
+        const size_t row_off = ((size_t)bh * n_blk + qb) * kk;
+        int n_tie = 0, n_out = 0;
+        // kept blocks in ascending order, ties at the threshold to the lowest indices
+        auto emit = [&](int c, uint32_t key, const Cut& cut) {
+            bool kept = false, tie = false;
+            if (c < n_blk) {
+                if (c == qb || need >= n_blk - 1) {
+                    kept = true;
+                } else if (need > 0) {
+                    tie = key == cut.thr;
+                    kept = key > cut.thr;
+                }
+            }
+            const unsigned long long tm = __ballot(tie);
+            if (tie) kept = n_tie + lanes_below(tm) < cut.rem;
+            n_tie += __popcll(tm);
+            const unsigned long long km = __ballot(kept);
+            const int pos = n_out + lanes_below(km);
+            if (kept && pos < kk) col_idx[row_off + pos] = c;  // exactly kk kept (total order)
+            n_out += __popcll(km);
+        };
+        const bool choose = need > 0 && need < n_blk - 1;
+        Cut cut = {0u, 0};
+        if constexpr (N > 0) {
+            uint32_t u[N];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) hw[4 * lane + j] = 0;
-            wave_lds_sync();
-            for (int i = 0; i < n_round; ++i) {
+            for (int i = 0; i < N; ++i) {
                 const int c = lane + 64 * i;
-                if (c < n_blk && c != qb) {
-                    const uint32_t key = order_key(row[c]);
-                    if ((key & thr_mask) == thr) atomicAdd(&hw[(key >> shift) & 255u], 1);
-                }
+                u[i] = c < n_blk && c != qb ? order_key(row[c]) : 0u;
             }
-            wave_lds_sync();
-            // lane L holds bins 4L .. 4L+3; S(t) counts the blocks with digit >= t
-            // and the threshold's digit is the t with S(t+1) < rem <= S(t)
-            int h[4], sum = 0;
+            if (choose) cut = cut_in_registers(u, need);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                h[j] = hw[4 * lane + j];
-                sum += h[j];
-            }
-            int incl = sum;  // inclusive sum over lanes 0 .. lane
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int y = __shfl_up(incl, d, 64);
-                if (lane >= d) incl += y;
-            }
-            const int tot = __shfl(incl, 63, 64);
-            int s_t = tot - incl;  // bins above this lane's four
-            int dig = -1, nrem = 0;
-#pragma unroll
-            for (int j = 3; j >= 0; --j) {
-                s_t += h[j];
-                if (h[j] > 0 && s_t >= rem && s_t - h[j] < rem) {
-                    dig = 4 * lane + j;
-                    nrem = rem - (s_t - h[j]);
-                }
-            }
-            const unsigned long long found = __ballot(dig >= 0);
-            const int src = __builtin_ctzll(found);  // exactly one lane finds it
-            thr |= (uint32_t)__shfl(dig, src, 64) << shift;
-            thr_mask |= 255u << shift;
-            rem = __shfl(nrem, src, 64);
-        }
-    }
-    // kept blocks in ascending order, ties at the threshold to the lowest indices
-    const size_t row_off = ((size_t)bh * n_blk + qb) * kk;
-    int n_tie = 0, n_out = 0;
-    for (int i = 0; i < n_round; ++i) {
-        const int c = lane + 64 * i;
-        bool kept = false, tie = false;
-        if (c < n_blk) {
-            if (c == qb || need >= n_blk - 1) {
-                kept = true;
-            } else if (need > 0) {
-                const uint32_t key = order_key(row[c]);
-                tie = key == thr;
-                kept = key > thr;
+            for (int i = 0; i < N; ++i) emit(lane + 64 * i, u[i], cut);
+        } else {
+            if (choose) cut = cut_by_radix(row, n_blk, qb, need, reinterpret_cast<int*>(sc + rows * n_blk) + 256 * w, lane);
+            for (int i = 0; 64 * i < n_blk; ++i) {
+                const int c = lane + 64 * i;
+                emit(c, c < n_blk ? order_key(row[c]) : 0u, cut);
             }
         }
-        const unsigned long long tm = __ballot(tie);
-        if (tie) kept = n_tie + lanes_below(tm) < rem;
-        n_tie += __popcll(tm);
-        const unsigned long long km_ = __ballot(kept);
-        const int pos = n_out + lanes_below(km_);
-        if (kept && pos < kk) col_idx[row_off + pos] = c;  // exactly kk kept (total order)
-        n_out += __popcll(km_);
-    }
-    if (lane == 0) {
-        row_ptr[(size_t)bh * (n_blk + 1) + qb] = (int32_t)row_off;
-        if (qb == n_blk - 1) row_ptr[(size_t)bh * (n_blk + 1) + n_blk] = (int32_t)(row_off + kk);
+        if (lane == 0) {
+            row_ptr[(size_t)bh * (n_blk + 1) + qb] = (int32_t)row_off;
+            if (qb == n_blk - 1) row_ptr[(size_t)bh * (n_blk + 1) + n_blk] = (int32_t)(row_off + kk);
+        }
     }
 }
 
@@ -308,12 +341,30 @@ hipError_t launch_dynamic_index(const DynIndexArgs& a, hipStream_t stream) {
                        a.block, a.n_blk, a.qsum, a.kmean);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    int rows = kSelRows;
-    while (rows > 1 && (size_t)rows * a.n_blk * sizeof(float) > (size_t)kSelScoreBytes) rows /= 2;
+    // a wave per 64 key blocks and two rows per wave, while their scores fit
+    const int n_tile = (a.n_blk + 63) / 64;
+    const int waves = n_tile < kSelWaves ? n_tile : kSelWaves;
+    int rows = 2 * waves;
+    const int fit = (int)(kSelScoreBytes / (a.n_blk * sizeof(float)));  // >= 2: n_blk <= 4096
+    if (rows > fit) rows = fit;
     const int n_grp = (a.n_blk + rows - 1) / rows;
-    const size_t lds = (size_t)rows * a.n_blk * sizeof(float);
-    hipLaunchKernelGGL(select_kernel, dim3(n_bh * n_grp), dim3(kSelThreads), lds, stream, a.qsum, a.kmean, a.D,
-                       a.n_blk, a.keep, rows, a.row_ptr, a.col_idx);
+    const size_t lds = (size_t)rows * a.n_blk * sizeof(float) + (a.n_blk > 64 * kSelRegs ? waves * 1024 : 0);
+    const dim3 grid(n_bh * n_grp), block(64 * waves);
+    auto go = [&](auto tiles) {
+        constexpr int N = decltype(tiles)::value;
+        if (a.D == 64)
+            hipLaunchKernelGGL((select_kernel<64, N>), grid, block, lds, stream, a.qsum, a.kmean, a.n_blk, a.keep, rows,
+                               a.row_ptr, a.col_idx);
+        else
+            hipLaunchKernelGGL((select_kernel<72, N>), grid, block, lds, stream, a.qsum, a.kmean, a.n_blk, a.keep, rows,
+                               a.row_ptr, a.col_idx);
+    };
+    if (n_tile <= 1) go(std::integral_constant<int, 1>{});
+    else if (n_tile <= 2) go(std::integral_constant<int, 2>{});
+    else if (n_tile <= 4) go(std::integral_constant<int, 4>{});
+    else if (n_tile <= 5) go(std::integral_constant<int, 5>{});
+    else if (n_tile <= kSelRegs) go(std::integral_constant<int, kSelRegs>{});
+    else go(std::integral_constant<int, 0>{});
     return hipGetLastError();
 }
 
