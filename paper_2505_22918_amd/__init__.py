@@ -110,6 +110,17 @@ def _ptr(t):
 
 def _check_qkv(q, k, v):
     torch = _torch()
+    # one expression for the usual case (a host tensor's get_device() is -1); anything
+    # else is named below
+    bf16 = torch.bfloat16
+    try:
+        shape, dev = q.shape, q.get_device()
+        if (q.is_cuda and q.dtype is bf16 and k.dtype is bf16 and v.dtype is bf16 and len(shape) == 4
+                and k.shape == shape and v.shape == shape and k.get_device() == dev and v.get_device() == dev
+                and q.is_contiguous() and k.is_contiguous() and v.is_contiguous()):
+            return _lib.RtDims(*shape)
+    except (AttributeError, TypeError):
+        pass
     for name, t in (("q", q), ("k", k), ("v", v)):
         if not isinstance(t, torch.Tensor) or not t.is_cuda:
             raise ValueError(f"{name} must be a CUDA tensor")
@@ -129,6 +140,14 @@ def _on_device(t, name, device):
         raise ValueError(f"{name} must be a CUDA tensor")
     if device is not None and t.device != device:
         raise ValueError(f"{name} is on {t.device}, expected {device}")
+
+
+def _same(t, dtype, shape, like):
+    """t is a contiguous tensor of this type and shape on `like`'s GPU."""
+    try:
+        return t.dtype is dtype and t.shape == shape and t.get_device() == like.get_device() and t.is_contiguous()
+    except (AttributeError, TypeError):
+        return False
 
 
 def _stat(t, shape, name, device=None):
@@ -152,11 +171,21 @@ def _out(out, like):
     contiguity, device), or a new one."""
     if out is None:
         return _torch().empty_like(like)
+    if _same(out, like.dtype, like.shape, like):
+        return out
     return _bf16(out, like.shape, "out", like.device)
 
 
-def _mask_on(mask, device):
+def _mask_on(mask, q):
     """The mask's device arrays must sit on the device of the attention inputs."""
+    dev = q.get_device()
+    row_ptr, col_idx = mask.row_ptr, mask.col_idx
+    try:
+        if row_ptr.get_device() == dev and col_idx.get_device() == dev:
+            return
+    except AttributeError:
+        pass
+    device = q.device
     for name, t in (("mask.row_ptr", mask.row_ptr), ("mask.col_idx", mask.col_idx)):
         _on_device(t, name, device)
 
@@ -308,7 +337,7 @@ def attn_sparse(q, k, v, mask: BlockMask, stats=True, out=None):
     torch = _torch()
     lib = _lib.load()
     dims = _check_qkv(q, k, v)
-    _mask_on(mask, q.device)
+    _mask_on(mask, q)
     o = _out(out, q)
     m = l = None
     if stats:
@@ -329,7 +358,7 @@ def attn_cache(q, k, v, mask: BlockMask, stats=True, out=None, ratio=True):
     torch = _torch()
     lib = _lib.load()
     dims = _check_qkv(q, k, v)
-    _mask_on(mask, q.device)
+    _mask_on(mask, q)
     o = _out(out, q)
     rho = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device) if ratio else None
     resid = torch.empty_like(q)
@@ -349,7 +378,7 @@ def attn_postmask(q, k, v, mask: BlockMask, out=None):
     torch = _torch()
     lib = _lib.load()
     dims = _check_qkv(q, k, v)
-    _mask_on(mask, q.device)
+    _mask_on(mask, q)
     o = _out(out, q)
     bsr = mask.c_struct()
     with _on(q):
@@ -391,10 +420,11 @@ def attn_sparse_reshape(q, k, v, mask: BlockMask, rho, resid, rho_delta=0.0, sta
     torch = _torch()
     lib = _lib.load()
     dims = _check_qkv(q, k, v)
-    _mask_on(mask, q.device)
-    if rho is not None:
+    _mask_on(mask, q)
+    if rho is not None and not _same(rho, torch.float32, q.shape[:3], q):
         _stat(rho, q.shape[:3], "rho", q.device)
-    _bf16(resid, q.shape, "resid", q.device)
+    if not _same(resid, torch.bfloat16, q.shape, q):
+        _bf16(resid, q.shape, "resid", q.device)
     o = _out(out, q)
     m = l = None
     if stats:
