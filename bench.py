@@ -487,7 +487,8 @@ def main():
         "frac": (gbs / PEAK_HBM_GBS) if bound == "hbm" else (tflops / PEAK_BF16_TFLOPS),
         "traffic": traffic,
         "traffic_over_algorithmic": (traffic / nbytes) if traffic else None,
-        "kernel": f"attn_fwd<{wl.D},{wl.block},reshape=true,stats=false,cache=false>",
+        "kernel": (f"attn_rows64<{wl.D},reshape=true,stats=false>" if wl.block == 64
+                   else f"attn_fwd<{wl.D},{wl.block},reshape=true,stats=false,cache=false>"),
         "algorithmic_bytes": nbytes,
         "algorithmic_flops": flops,
         "executed_mfma_flops": exec_flops,

@@ -17,9 +17,9 @@
 // beside its own; 131 instructions per 32-key chunk and 64 rows) and by power:
 // with zero queries, keys and values the same instructions run 21 % faster, as a
 // large bf16 product does.  Measured, before -> now: PixArt-Sigma-2K dense with
-// statistics (32 heads, 16384 tokens, D = 72) 3998 -> 2582 us (0.96 PFLOP/s of real
-// dims), CogVideoX caching step (60 heads, 17776 tokens, D = 64) 5739 -> 5266 us, of
-// which the sparse walk is 235; PixArt-Sigma-1024 caching step 289 -> 201 us.
+// statistics (32 heads, 16384 tokens, D = 72) 3936 -> 2474 us (1.0 PFLOP/s of real
+// dims), CogVideoX caching step (60 heads, 17776 tokens, D = 64) 5510 -> 4907 us, of
+// which the sparse walk is 225; PixArt-Sigma-1024 caching step 289 -> 191 us.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
     // ---- epilogue -------------------------------------------------------------------------
     // lane (hi, l32) holds 16 head dims 32 dt + 16 hi .. of query l32 per tile and dt,
-    // and in the tail lanes 0 .. 31 hold 4 head dims of query 16 h + lane % 16
+    // and in the tail 4 head dims of query 16 h + lane % 16 of tile hi
     const bool split = CACHE && n_kept < n64;
     float inv2[2], rho2[2];
     // four output values of one row from accumulators, 1 / l, rho and O_s
