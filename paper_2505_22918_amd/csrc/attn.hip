@@ -873,7 +873,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     const int nrow = (T - row0) < BS ? (T - row0) : BS;
 
     Tiles<D, STATS, STATS, ZERO> t;
-    t.init(lds, lane, T, a.scale_log2);
+    t.init(lds, T, a.scale_log2);
     // Q first, so that its HBM latency runs under the reads of the CSR row below
     t.load_q(a.q + head_off + (size_t)row0 * D, nrow);
     float rho_r[2];

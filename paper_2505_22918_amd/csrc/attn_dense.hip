@@ -93,7 +93,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const i32x4 v_rs = buffer_rsrc(a.v + head_off, T * D * 2);
 
     Tiles<D, STATS, STATS || CACHE, ZERO> t;
-    t.init(lds, lane, T, a.scale_log2);
+    t.init(lds, T, a.scale_log2);
     t.load_q(a.q + head_off + (size_t)row0 * D, nrow);
     for (int i = threadIdx.x * 16; i < ZLEN; i += 64 * W * 16) *(lds_u32x4*)(lds + ZERO + i) = u32x4{};
 
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     // against it in the first 8 bytes of the residual row.
     const bool has_in = CACHE && n_kept > 0;
     auto kept_stat = [&](int qt, int i) {
-        const int row = row0 + qt * 32 + l32;
+        const int row = row0 + qt * 32 + t.l32;
         return row < T ? reinterpret_cast<const float*>(a.resid_out + head_off + (size_t)row * D)[i] : 0.f;
     };
     if (has_in) {
@@ -210,6 +210,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     if (!live) return;
 
     // ---- epilogue -------------------------------------------------------------------------
+    t.lanes();
     // lane (hi, l32) holds 16 head dims 32 dt + 16 hi .. of query l32 per tile and dt,
     // and in the tail 4 head dims of query 16 h + lane % 16 of tile hi
     const bool split = CACHE && n_kept < n64;
@@ -237,7 +238,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     };
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
-        const int row = row0 + qt * 32 + l32;
+        const int row = row0 + qt * 32 + t.l32;
         const float ls = pair_sum(t.l_run[qt]);
         float li = 0.f;
         if (has_in) li = kept_stat(qt, 1) * __builtin_amdgcn_exp2f((kept_stat(qt, 0) - t.m_run[qt]) * a.scale_log2);
@@ -247,7 +248,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         inv2[qt] = inv;
         rho2[qt] = rho;
         if (STATS) t.m_top[qt] = pair_max(t.m_top[qt]);
-        if (hi == 0 && row < T) {
+        if (t.hi == 0 && row < T) {
             const size_t si = (size_t)bh * T + row;
             if (CACHE && a.rho_out) a.rho_out[si] = rho;
             if (STATS) {
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 if (row < T) {
-                    const size_t off = head_off + (size_t)row * D + 8 * (4 * dt + 2 * hi + u);
+                    const size_t off = head_off + (size_t)row * D + 8 * (4 * dt + 2 * t.hi + u);
                     u32x4 os = {};
                     if (has_in) os = *reinterpret_cast<const u32x4*>(a.o + off);
                     float acc[8];
@@ -280,9 +281,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const float iv = t.tail_bcast(inv2[0], inv2[1], h), rh = t.tail_bcast(rho2[0], rho2[1], h);
-            const int row = row0 + 32 * hi + 16 * h + (lane & 15);
+            const int row = row0 + 32 * t.hi + 16 * h + (t.lane & 15);
             if (row < T) {
-                const size_t off = head_off + (size_t)row * D + 64 + 4 * ((lane >> 4) & 1);
+                const size_t off = head_off + (size_t)row * D + 64 + 4 * ((t.lane >> 4) & 1);
                 uint32_t os[2] = {0u, 0u}, o[2], r[2];
                 if (has_in) {
                     os[0] = reinterpret_cast<const uint32_t*>(a.o + off)[0];

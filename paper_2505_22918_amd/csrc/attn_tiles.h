@@ -18,11 +18,12 @@
 // softmax, each tile's scores stay in one set of registers (the rare rescale finds them
 // there), and K and V operands are read once for both tiles.
 //
-// 72-wide heads.  The 8 head dims past 64 take one k-step of Q K^T (tile 0's query
-// values in the lower half of the lanes, tile 1's in the upper) and one 16x16x32
-// product per 16 queries of P V, both tiles into one accumulator: 320 matrix cycles a
-// chunk and tile instead of 352 with a third 32-row tile, and 233-247 registers instead
-// of 370-420, so these heads too run two waves per SIMD.
+// 72-wide heads.  The 8 head dims past 64 take one k-step of Q K^T (half of it zeros) and
+// one 16x16x32 product per 16 queries of P V, both tiles into one accumulator (a
+// tile's V operand is zero in the rows of the other): 320 matrix cycles a chunk and tile
+// instead of 352 with a third 32-row tile, and 233-243 registers instead of 370-420, so
+// these heads too run two waves per SIMD.  The zeros never meet a NaN or an infinity,
+// so that one query row's cannot reach another's.
 //
 // Softmax.  The running max starts at the first chunk's max and moves only
 // when a chunk's probabilities against it reach 2^64 (far below fp32 and bf16
@@ -71,9 +72,9 @@ struct Tiles {
     int k_rd, v_rd, t_rd;
     int T, full_lim;
     float c2;  // log2(e) / sqrt(D)
-    // Of a 72-wide head's last 8 dims, lanes of half 0 hold query tile 0's and lanes of
-    // half 1 tile 1's: each tile's tail product has zeros in K for the other half.
-    bf16x8 qop[2][DS], qtl;
+    // Of a 72-wide head's last 8 dims, tile Q's queries sit in lanes of half Q, with
+    // zeros in the other half and in K's there.
+    bf16x8 qop[2][DS], qtl[2];
     f32x16 oacc[2][2];
     f32x4 tacc[2];  // tail of O^T for 16 queries: rows 0-7 tile 0's dims, 8-15 tile 1's
     float m_run[2], m_top[2], l_run[2];
@@ -84,11 +85,15 @@ struct Tiles {
     bf16x8 kt1, vt1;     // the tails of both, for query tile 1
     bf16x8 kt0, vt0;     // and for tile 0, read by its own phase
 
-    __device__ __forceinline__ void init(lds_u8* smem, int lane_, int T_, float scale_log2) {
-        lds = smem;
-        lane = lane_;
+    // the lane's constants, formed anew: after the walk, so that none is held throughout it
+    __device__ __forceinline__ void lanes() {
+        lane = fresh(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)));
         l32 = lane & 31;
         hi = lane >> 5;
+    }
+    __device__ __forceinline__ void init(lds_u8* smem, int T_, float scale_log2) {
+        lds = smem;
+        lanes();
         T = T_;
         full_lim = (T - 32) * (D * 2);
         c2 = scale_log2;
@@ -121,7 +126,7 @@ struct Tiles {
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) vop[k] = bf16x8{};
-        kt0 = kt1 = vt0 = vt1 = qtl = bf16x8{};
+        kt0 = kt1 = vt0 = vt1 = qtl[0] = qtl[1] = bf16x8{};
     }
 
     // Q^T operands: lane holds query l32 of tile qt, head dims 16s + 8hi .. +7 (zero past
@@ -129,21 +134,22 @@ struct Tiles {
     __device__ __forceinline__ void load_q(const uint16_t* rows, int nrow) {
         const __amdgpu_buffer_rsrc_t rs =
             __builtin_amdgcn_make_buffer_rsrc((void*)rows, (short)0, nrow * D * 2, 0x00020000);
-        auto load = [&](int row, int ch) {
-            return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, row * (D * 2) + ch * 16, 0, 0));
+        auto load = [&](int off) {
+            return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
         };
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt) {
+            const int row = (qt * 32 + l32) * (D * 2);
 #pragma unroll
-            for (int s = 0; s < DS; ++s) qop[qt][s] = load(qt * 32 + l32, 2 * s + hi);
+            for (int s = 0; s < DS; ++s) qop[qt][s] = load(row + (2 * s + hi) * 16);
+            if (TAIL) qtl[qt] = load(hi == qt ? row + 128 : kOob);
         }
-        if (TAIL) qtl = load(hi * 32 + l32, 8);
     }
     // Q has landed: no wait of the compiler's in the walk
     __device__ __forceinline__ void settle_q() {
 #pragma unroll
         for (int s = 0; s < DS; ++s) asm volatile("" : "+v"(qop[0][s]), "+v"(qop[1][s]));
-        if (TAIL) asm volatile("" : "+v"(qtl));
+        if (TAIL) asm volatile("" : "+v"(qtl[0]), "+v"(qtl[1]));
     }
 
     // row max of one chunk; lane holds keys 8j + 4hi + i for acc index 4j + i, the
@@ -229,7 +235,7 @@ struct Tiles {
         f32x16 x = {};
 #pragma unroll
         for (int s = 0; s < DS; ++s) x = mma(kop[s], qop[Q][s], x);
-        if (TAIL) x = mma(k_tail(k_rd, ko, Q), qtl, x);
+        if (TAIL) x = mma(k_tail(k_rd, ko, Q), qtl[Q], x);
         mask(cb, x);
         return x;
     }
@@ -318,7 +324,7 @@ struct Tiles {
         // the max is taken here, not moved behind the last read of the scores
         if (STATS) asm volatile("" : "+v"(m_top[Q]));
         if (TAIL) {
-            if (QK) sn = mma(Q ? kt0 : kt1, qtl, sn);
+            if (QK) sn = mma(Q ? kt0 : kt1, qtl[R], sn);
             if (PV) tail_mma(Q ? vt0 : vt1, pk[R]);
             RT_FENCE;
             if (Q == 1) {
@@ -333,7 +339,10 @@ struct Tiles {
                 for (int x = 0; x < 8; ++x) pk[Q][x] = 0u;
                 ls = 0.f;
             } else {
-                // A probability reached 2^64: O and l move to the chunk's max.
+                // A probability reached 2^64: O and l move to the chunk's max.  The tails'
+                // product would carry a NaN probability into the other tile (zero rows of V
+                // times NaN): l alone takes it, and with l the row's output is NaN.
+                auto number = [](float p) { return TAIL ? fminf(p, 2.0f) : p; };  // 2 for a NaN
                 const float mnew = fmaxf(m_run[Q], chunk_max(sc));
                 const float alpha = __builtin_amdgcn_exp2f((m_run[Q] - mnew) * c2);
                 l_run[Q] *= alpha;
@@ -350,8 +359,8 @@ struct Tiles {
                     RT_FENCE;
 #pragma unroll
                     for (int y = 0; y < 4; ++y) e[y] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[x + y], c2, -mn));
-                    pk[Q][x / 2] = pack_bf16(e[0], e[1]);
-                    pk[Q][x / 2 + 1] = pack_bf16(e[2], e[3]);
+                    pk[Q][x / 2] = pack_bf16(number(e[0]), number(e[1]));
+                    pk[Q][x / 2 + 1] = pack_bf16(number(e[2]), number(e[3]));
                     part = (e[0] + e[1]) + (e[2] + e[3]);
                     if (x == 0) sa = part;
                     if (x == 4) sb = part;
@@ -360,7 +369,7 @@ struct Tiles {
                 }
                 RT_FENCE;
                 ls = sa + sb;
-                if (!F32_SUM) ls = bf16_sum(pk[Q]);
+                if (!F32_SUM && !(TAIL && ls != ls)) ls = bf16_sum(pk[Q]);
             }
         }
         l_run[Q] += ls;
