@@ -1039,8 +1039,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         if (STATS) t.m_top[qt] = pair_max(t.m_top[qt]);
         if (STATS && hi == 0 && row < T) {
             const size_t si = ((size_t)bh * T + row) * a.stat_stride;
+            // before the second half of a caching step (rows D / 2 floats apart) the sum is
+            // against a finite max: a row that kept no key leaves 0, not 0 * exp2(inf)
+            const float ref = a.stat_stride == 1 ? t.m_top[qt] : fmaxf(t.m_top[qt], -1e30f);
             if (a.row_max) a.row_max[si] = t.m_top[qt] * a.scale_nat;
-            if (a.row_sum) a.row_sum[si] = l_tot * __builtin_amdgcn_exp2f((t.m_run[qt] - t.m_top[qt]) * a.scale_log2);
+            if (a.row_sum) a.row_sum[si] = l_tot * __builtin_amdgcn_exp2f((t.m_run[qt] - ref) * a.scale_log2);
         }
         const lds_u8* Rs = lds + ((n + qt) & 1) * HALF;  // residual rows: the K stage of chunk n + qt
 #pragma unroll

@@ -45,7 +45,7 @@ hipError_t launch_attention(const AttnArgs& a, int D, int block, AttnMode mode, 
 // The walks over every key block (attn_dense.hip), called by launch_attention:
 // dense attention, or (cache) the second half of a caching step over 64-token
 // blocks: o holds O_s and the first 8 bytes of each resid_out row the kept keys'
-// largest unscaled score and their exp-sum against it.
+// largest unscaled score m and their exp-sum against max(m, -1e30).
 hipError_t launch_attention_dense(const AttnArgs& a, int D, bool cache, hipStream_t stream);
 
 hipError_t launch_cache_build(const uint16_t* o_full, const float* m_full, const float* l_full,
