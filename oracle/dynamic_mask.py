@@ -16,9 +16,9 @@ and query block qb:
     divided (one correctly rounded fp32 division) by its token count, so a
     short last block is compared by its mean;
   * the block score is their dot product, accumulated in fp32 in ascending head
-    dim with a separately rounded product and sum per term (no fused
-    multiply-add); the common positive factors of a row (the query mean's 1/n
-    and Eq.2's 1/sqrt(d_h)) do not change its ranking and are left out;
+    dim by fused multiply-adds (the exact product joins the sum with one
+    rounding per term); the common positive factors of a row (the query mean's
+    1/n and Eq.2's 1/sqrt(d_h)) do not change its ranking and are left out;
   * query block qb keeps its own block (so S_i is never empty, as Eq.5
     requires) and the keep - 1 highest-scoring other blocks, a tie going to the
     lower index; the row is stored in ascending block order;
@@ -34,7 +34,7 @@ from __future__ import annotations
 
 import numpy as np
 
-__all__ = ["pooled", "block_scores", "select", "dynamic_mask", "dynamic_mask_f64_reference"]
+__all__ = ["pooled", "fma32", "block_scores", "select", "dynamic_mask", "dynamic_mask_f64_reference"]
 
 
 def _blocks(T, block):
@@ -61,17 +61,40 @@ def pooled(x, block):
     return sums, counts
 
 
+def fma32(a, b, c):
+    """a * b + c of fp32 arrays, rounded once to fp32 (nearest even).
+
+    The float64 product of two fp32 values is exact (48 bits).  The float64 sum
+    may be inexact, and rounding it again to fp32 is then wrong where it sits on
+    the middle between two fp32 values (or is subnormal in fp32, where the middle
+    is elsewhere); there an even one is first moved to its odd neighbour on the
+    side of the exact value (the error term of Knuth's two-sum says which)."""
+    c = np.asarray(c, dtype=np.float64)
+    with np.errstate(invalid="ignore", over="ignore"):
+        p = np.multiply(a, b, dtype=np.float64)
+        s = p + c
+        near = ((s.view(np.int64) & 0x1fffffff) == 0x10000000) | (np.abs(s) < 2.0 ** -125)
+        if near.any():
+            near &= s.view(np.int64) & 1 == 0
+            t = s - p
+            err = (p - (s - t)) + (c - t)
+            s = np.where(near & (err != 0) & np.isfinite(err), np.nextafter(s, np.copysign(np.inf, err)), s)
+        return s.astype(np.float32)
+
+
 def block_scores(q, k, block):
     """The block score matrix [n_blk, n_blk] (float32) of one head."""
     qsum, _ = pooled(q, block)
     ksum, kcnt = pooled(k, block)
     kmean = (ksum / kcnt[:, None].astype(np.float32)).astype(np.float32)
     nb, d = qsum.shape
-    acc = np.zeros((nb, nb), dtype=np.float32)
-    for j in range(d):  # ascending head dim; product and sum rounded separately
-        prod = (qsum[:, j][:, None] * kmean[:, j][None, :]).astype(np.float32)
-        acc = (acc + prod).astype(np.float32)
-    return acc
+    out = np.empty((nb, nb), dtype=np.float32)
+    for i in range(0, nb, 32):  # a few rows at a time stay in cache
+        acc = np.zeros((min(32, nb - i), nb), dtype=np.float32)
+        for j in range(d):  # ascending head dim, one rounding per term
+            acc = fma32(qsum[i:i + 32, j][:, None], kmean[:, j][None, :], acc)
+        out[i:i + 32] = acc
+    return out
 
 
 def select(scores, keep):

@@ -29,3 +29,18 @@ def test_selection_at_tile_counts(gpu, D, n):
         rp, ci = dm.dynamic_mask(synth.bf16_bits_to_f32(q), synth.bf16_bits_to_f32(k), block, keep)
         assert np.array_equal(mask.row_ptr.cpu().numpy(), rp)
         assert np.array_equal(mask.col_idx.cpu().numpy(), ci)
+
+
+@pytest.mark.parametrize("D", [64, 72])
+@pytest.mark.parametrize("block", [32, 64])
+def test_near_tie_is_ranked_as_the_oracle_does(gpu, D, block):
+    """Two keys whose scores are equal with product and sum rounded separately, and one last bit apart
+    by fused multiply-adds."""
+    from test_oracle_dynamic import near_tie
+
+    print(f"[select] near tie D={D} block={block}", flush=True)
+    q, k = near_tie(D, block)
+    mask = rt.dynamic_index(*(to_dev(synth.f32_to_bf16_bits(x)[None, None]) for x in (q, k)), block, 2)
+    rp, ci = dm.dynamic_mask(q[None, None], k[None, None], block, 2)
+    assert list(ci[:2]) == [0, 2]
+    assert np.array_equal(mask.col_idx.cpu().numpy(), ci)

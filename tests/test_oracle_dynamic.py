@@ -182,3 +182,66 @@ def test_hand_derived_golden_masks():
             rp, ci = dm.dynamic_mask(q, k, c["block"], int(keep))
             got = [list(ci[rp[r]:rp[r + 1]]) for r in range(len(rows))]
             assert got == rows, (c["name"], keep, got)
+
+
+def test_fma32_rounds_once():
+    """Against exact rational arithmetic: random operands, sums on and next to the middle
+    between two fp32 values, cancellation, subnormal results and overflow."""
+    from fractions import Fraction
+
+    rng = np.random.default_rng(4)
+    f32 = lambda x: np.asarray(x, dtype=np.float32)
+    a, b = f32(rng.standard_normal(400)), f32(rng.standard_normal(400))
+    c = np.concatenate([f32(rng.standard_normal(100)), -(a[100:200] * b[100:200]), f32(2.0 ** 30) * a[200:300],
+                        f32(2.0 ** -30) * a[300:]])
+    # (2^12 + 1)^2 + c: exact sums half way between fp32 values, and a 2^-40 off it
+    one = f32([4097.0, 4097.0, 4097.0, 2.0 ** -70, 2.0 ** -75, 3e38, 2.0 ** 24, 2.0 ** 24])
+    two = f32([4097.0, 4097.0, 4097.0, 2.0 ** -70, 2.0 ** -75, 10.0, 1.0 + 2.0 ** -23, -(1.0 + 2.0 ** -23)])
+    add = f32([0.0, 2.0 ** -40, -2.0 ** -40, 2.0 ** -149, 2.0 ** -149, 1.0, 1.0 + 2.0 ** -23, 3.0])
+    a, b, c = np.concatenate([a, one]), np.concatenate([b, two]), np.concatenate([c, add])
+    for x, y, z, got in zip(a, b, c, dm.fma32(a, b, c)):
+        exact = Fraction(float(x)) * Fraction(float(y)) + Fraction(float(z))
+        if abs(exact) > Fraction(float(np.finfo(np.float32).max)):
+            assert np.isinf(got) and (got > 0) == (exact > 0)
+            continue
+        near = [np.nextafter(got, f32(-np.inf)), got, np.nextafter(got, f32(np.inf))]
+        off = [abs(Fraction(float(n)) - exact) if np.isfinite(n) else None for n in near]
+        assert all(o is None or off[1] <= o for o in off), (x, y, z)
+        if off[1] in (off[0], off[2]):  # a tie goes to the even one
+            assert got.view(np.int32) % 2 == 0
+    assert np.isnan(dm.fma32(f32([np.inf]), f32([0.0]), f32([1.0]))[0])
+    assert dm.fma32(f32([np.inf]), f32([2.0]), f32([1.0]))[0] == np.inf
+
+
+def near_tie(d, block):
+    """bf16 q, k [3 blocks, d] whose block 0 ranks block 2 above block 1 by fused multiply-adds
+    and sees a tie (block 1 first) when product and sum are rounded separately.
+
+    The pooled query is (a, a, 0, ..), the key means (x, y, 0, ..) and (y, x, 0, ..):
+    fl(a x) + fl(a y) is the same in either order, fma(a, y, fl(a x)) is not."""
+    a, x, y = 14139351, 16358627, 13845055
+
+    def rows(n):  # three rows of 8-bit significands that sum to the 24-bit whole number n
+        hi, mid = n >> 16 << 16, n >> 8 & 255
+        return np.array([hi, mid << 8, n & 255], dtype=np.float32)
+
+    q = np.zeros((3 * block, d), dtype=np.float32)
+    k = np.zeros((3 * block, d), dtype=np.float32)
+    q[:3, 0] = q[:3, 1] = rows(a)
+    scale = block // 32  # the mean of 64 tokens has the sum of 32 in half a block
+    for at, (u, v) in ((block, (x, y)), (2 * block, (y, x))):
+        k[at:at + 3, 0], k[at:at + 3, 1] = scale * rows(u), scale * rows(v)
+    assert np.array_equal(_bf16(q), q) and np.array_equal(_bf16(k), k)
+    return q, k
+
+
+@pytest.mark.parametrize("block", [32, 64])
+def test_near_tie_is_ranked_by_fused_multiply_adds(block):
+    q, k = near_tie(64, block)
+    s = dm.block_scores(q, k, block)
+    assert s[0, 2] > s[0, 1]
+    rp, ci = dm.select(s, keep=2)
+    assert list(ci[:2]) == [0, 2]
+    qs, km = dm.pooled(q, block)[0], dm.pooled(k, block)[0] / np.float32(block)
+    apart = [np.float32(qs[0, 0] * m[0]) + np.float32(qs[0, 1] * m[1]) for m in km]
+    assert apart[1] == apart[2]
