@@ -7,8 +7,9 @@
 //   rt_attn_sparse_reshape  Eq.5, then Eq.9 (rho, ramped) and Eq.10 (residual)
 //
 // Masks of 64-token blocks run attn_rows64 below: one wavefront per 64 query rows,
-// the two-tile walk of attn_tiles.h.  Masks of 32-token blocks, and caching steps
-// that are not worth two kernels, run attn_fwd, which this comment describes.
+// the two-tile walk of attn_tiles.h.  Masks of 32-token blocks, 64-wide heads whose few
+// waves gain nothing from it, and caching steps that are not worth two kernels run
+// attn_fwd, which this comment describes.
 //
 // One workgroup is one wavefront that owns one query block (32 or 64 rows) of
 // one (batch, head) and walks the key blocks of its CSR row in 32-key chunks:
@@ -792,7 +793,7 @@ void attn_fwd(AttnArgs a) {
         // output is added to the residual unscaled
         if (RESHAPE && a.rho) factor *= fminf(1.0f, rho_r[qt] + a.rho_delta);
         if (STATS && hi == 0 && row < T) {
-            const size_t si = ((size_t)bh * T + row) * a.stat_stride;
+            const size_t si = (size_t)bh * T + row;
             if (a.row_max) a.row_max[si] = m_top[qt] * a.scale_nat;
             if (a.row_sum) a.row_sum[si] = l_tot * __builtin_amdgcn_exp2f((m_run[qt] - m_top[qt]) * c2);
         }
@@ -1121,18 +1122,37 @@ hipError_t launch_one(const AttnArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Whether a walk of 64-wide heads over 64-token blocks is faster as attn_fwd than as
+// attn_rows64.  The chip holds 1024 such waves one to a SIMD and 2048 two to a SIMD.  A
+// wave that is alone, or among rounds that fill unevenly, gains nothing from
+// attn_rows64's interleaving and pays for its two half steps (attn_fwd against
+// attn_rows64: 256 items of 16 kept blocks 19.3 us and 20.6, fused 20.7 and 21.3; 1024 of 32
+// 41.2 and 42.3; 3072 of 4 25.1 and 25.8, fused 27.2 and 28.2); from four rounds
+// on, and where one round puts two waves on some SIMDs, it is the faster (16680
+// of 9 fused 226 and 221; 1280 of 4 13.6 and 13.0).  With statistics, which
+// attn_fwd pays more for, only rows of one or two blocks in uneven rounds are faster there
+// (3840 of 2: 24.4 and 25.4; of 8: 49.6 and 48.2).
+bool few_waves(const AttnArgs& a) {
+    const int64_t blocks = a.dense ? a.n_blk : a.nnz / ((int64_t)a.n_masks * a.n_blk);  // kept by a row
+    const bool uneven = a.n_items > 2048 && a.n_items <= 6144;
+    if (a.row_max || a.row_sum) return uneven && blocks <= 2;
+    return uneven || a.n_items <= 512 || (a.n_items <= 1024 && blocks > 16);
+}
+
 template <int D, int BS>
 hipError_t launch_db(const AttnArgs& a, AttnMode mode, hipStream_t stream) {
     const bool stats = a.row_max != nullptr || a.row_sum != nullptr;
     if (mode == kAttnCache)
         return stats ? launch_one<D, BS, false, true, true>(a, stream) : launch_one<D, BS, false, false, true>(a, stream);
     if constexpr (BS == 64) {
-        return launch_rows64<D>(a, mode, stream);
-    } else if (mode == kAttnReshape) {
-        return stats ? launch_one<D, BS, true, true, false>(a, stream) : launch_one<D, BS, true, false, false>(a, stream);
-    } else {
+        if (D != 64 || !few_waves(a)) return launch_rows64<D>(a, mode, stream);
+    }
+    if constexpr (BS == 32 || D == 64) {
+        if (mode == kAttnReshape)
+            return stats ? launch_one<D, BS, true, true, false>(a, stream) : launch_one<D, BS, true, false, false>(a, stream);
         return stats ? launch_one<D, BS, false, true, false>(a, stream) : launch_one<D, BS, false, false, false>(a, stream);
     }
+    return hipErrorInvalidValue;  // not reached
 }
 
 }  // namespace
@@ -1190,7 +1210,7 @@ hipError_t launch_attention(const AttnArgs& a, int D, int block, AttnMode mode, 
         s.row_sum = s.row_max + 1;
         s.stat_stride = D / 2;
         s.scale_nat = 1.0f;
-        const hipError_t e = D == 64 ? launch_db<64, 64>(s, kAttn, stream) : launch_db<72, 64>(s, kAttn, stream);
+        const hipError_t e = D == 64 ? launch_rows64<64>(s, kAttn, stream) : launch_rows64<72>(s, kAttn, stream);
         return e != hipSuccess ? e : launch_attention_dense(a, D, true, stream);
     }
     if (D == 64) return block == 64 ? launch_db<64, 64>(a, mode, stream) : launch_db<64, 32>(a, mode, stream);
