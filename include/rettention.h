@@ -191,7 +191,7 @@ rt_status rt_dynamic_index_noalloc(const void* q, const void* k, rt_dims dims, i
 /* Dense attention with row statistics, Eq.1 with the Eq.4 denominator.
  * q, k, v: device bf16 [B,H,T,D]; o: device bf16 [B,H,T,D] (written);
  * row_max, row_sum: device fp32 [B,H,T] (written, either may be NULL).
- * The query tiling uses `block` rows (32 or 64). */
+ * `block` is 32 or 64 and does not change the result: the query tiling follows the shape. */
 rt_status rt_attn_full(const void* q, const void* k, const void* v, rt_dims dims, int32_t block,
                        void* o, float* row_max, float* row_sum, void* stream);
 

@@ -1136,7 +1136,7 @@ bool few_waves(const AttnArgs& a) {
     const int64_t blocks = a.dense ? a.n_blk : a.nnz / ((int64_t)a.n_masks * a.n_blk);  // kept by a row
     const bool uneven = a.n_items > 2048 && a.n_items <= 6144;
     if (a.row_max || a.row_sum) return uneven && blocks <= 2;
-    return uneven || a.n_items <= 512 || (a.n_items <= 1024 && blocks > 16);
+    return uneven || a.n_items <= 512 || (a.n_items <= 1024 && blocks >= 16);
 }
 
 template <int D, int BS>
@@ -1159,32 +1159,46 @@ hipError_t launch_db(const AttnArgs& a, AttnMode mode, hipStream_t stream) {
 
 namespace {
 
-// The same walk over query blocks of 32 rows (dense: any block gives the same keys
-// in the same order).
-AttnArgs in_rows_of_32(AttnArgs a) {
+// Dense attention over query blocks of `rows` rows: any block gives the same keys in the
+// same order.
+AttnArgs in_rows_of(AttnArgs a, int rows) {
     const int64_t n_bh = a.n_items / a.n_blk;
-    a.n_blk = (a.T + 31) / 32;
+    a.n_blk = (a.T + rows - 1) / rows;
     a.n_items = (int32_t)(n_bh * a.n_blk);
     a.per_xcd = (a.n_items + 7) / 8;
     return a;
 }
 
-// Dense attention.  Up to 1024 waves of 32 rows (one per SIMD of the chip) a chunk's
-// latency bounds the call, and the shortest walk wins: waves of 32 rows with a
-// ring each (D = 64, two heads of 4096 tokens: 43 us, against 66 in rows of 64 and 74 with
-// a shared ring; D = 72: 70, 110, 84).  Above, the matrix and vector units do: waves
-// of 64 rows over a shared ring (D = 72, 32 heads of 4096: 157 us, against 266 and 228).
-// In between, a 64-wide head without statistics keeps the private ring while there is at
-// most one wave of 64 rows per SIMD (8 heads of 8192: 145 us, 150 shared; with
-// statistics 162 and 148).
-hipError_t launch_dense(const AttnArgs& a, int D, int block, hipStream_t stream) {
-    const int64_t n_bh = a.n_items / a.n_blk;
-    if (n_bh * ((a.T + 31) / 32) <= 1024)
-        return D == 64 ? launch_db<64, 32>(in_rows_of_32(a), kAttn, stream)
-                       : launch_db<72, 32>(in_rows_of_32(a), kAttn, stream);
-    if (D == 64 && block == 64 && a.n_items <= 1024 && !a.row_max && !a.row_sum)
-        return launch_db<64, 64>(a, kAttn, stream);
-    return launch_attention_dense(a, D, false, stream);
+// Dense attention: waves of 32 rows (attn_fwd), of 64 rows with a ring each (attn_rows64 or
+// attn_fwd), or four of 64 rows over a shared ring (attn_dense).
+//  - Up to 1024 waves of 32 rows (one per SIMD of the chip) a chunk's latency bounds the
+//    call, and the shortest walk wins (D = 64, two heads of 4096 tokens: 43 us, against 66 in
+//    rows of 64 and 74 with the shared ring; D = 72: 70, 110, 84); at D = 64 up to 1536 such waves of
+//    at most 14 blocks (72 heads of 512: 12.2, 12.6, 13.6).
+//  - Where the last wave of 64 rows would be half empty, short heads take rows of 32: to 160
+//    tokens at D = 64 (800 heads 15.0, 18.3, 23.0), 96 at D = 72 (1000 heads 12.7, 14.2, 20.7),
+//    224 while two rounds hold all (D = 64, 600 heads: 19.4, 21.3, 23.0), and 448 while few
+//    SIMDs hold two (D = 72, 120 heads of 288: 10.3, 11.3, 12.8).
+//  - Up to 14 blocks of 64 a wave's own ring wins: of a workgroup of four the waves past
+//    the last row walk for nothing (D = 72: 4096 heads of 64 24.7 and 42.7; 512 of 320 28.6 and
+//    35.6; 300 of 832 73.6 and 88.8).  Where none is idle and there are many of them
+//    the shared ring does (D = 72: 1024 heads of 512 113 and 104; 1024 of 250 39.0 and 40.0, 4096
+//    147 and 136).
+//  - Longer walks take the shared ring (D = 72, 32 heads of 4096: own rings 166, shared 156)
+//    but for 64-wide heads without statistics at one wave per SIMD (16 heads of 4096: attn_fwd
+//    75.5, shared 76.7; 9 heads 70.2 and 72.6).
+hipError_t launch_dense(const AttnArgs& a, int D, hipStream_t stream) {
+    const AttnArgs a32 = in_rows_of(a, 32), a64 = in_rows_of(a, 64);
+    const int waves = a32.n_items, blocks = a64.n_blk;
+    bool rows32 = waves <= 1024 || (D == 64 && waves <= 1536 && blocks <= 14);
+    if (a32.n_blk & 1)
+        rows32 |= a.T <= (D == 64 ? 160 : 96) || (a.T <= 224 && waves <= 4608) || (a.T <= 448 && waves <= 1280);
+    if (rows32) return D == 64 ? launch_db<64, 32>(a32, kAttn, stream) : launch_db<72, 32>(a32, kAttn, stream);
+    const bool alone = D == 64 && !a.row_max && !a.row_sum && a64.n_items <= 1024;
+    if (blocks > 14 ? !alone : blocks % 4 == 0 && a64.n_items > 4096)
+        return launch_attention_dense(a, D, false, stream);
+    if (D == 72) return launch_rows64<72>(a64, kAttn, stream);
+    return blocks <= 3 ? launch_rows64<64>(a64, kAttn, stream) : launch_db<64, 64>(a64, kAttn, stream);
 }
 
 // Whether a caching step over 64-token blocks runs as the sparse walk and then the dense
@@ -1203,7 +1217,7 @@ bool cache_in_two(const AttnArgs& a, int D) {
 }  // namespace
 
 hipError_t launch_attention(const AttnArgs& a, int D, int block, AttnMode mode, hipStream_t stream) {
-    if (mode == kAttn && a.dense) return launch_dense(a, D, block, stream);
+    if (mode == kAttn && a.dense) return launch_dense(a, D, stream);
     if (mode == kAttnCache && block == 64 && !a.postmask && cache_in_two(a, D)) {
         AttnArgs s = a;  // O_s to o, the kept keys' statistics to the residual rows
         s.row_max = reinterpret_cast<float*>(a.resid_out);
