@@ -1202,16 +1202,35 @@ hipError_t launch_dense(const AttnArgs& a, int D, hipStream_t stream) {
 }
 
 // Whether a caching step over 64-token blocks runs as the sparse walk and then the dense
-// walk over the dropped keys.  The dense walk spends its time on every block, so the
-// two cost 1 + (kept share) dense walks: worth it while that stays below its gain
-// over the single kernel (1.16x at D = 64, 1.5x at D = 72, CogVideoX and PixArt-Sigma-2K
-// shapes).  Short walks do not pay for the second launch (D = 64: 1024 tokens
-// 31 us against 28, 2048 tokens 51 and 51, 4096 tokens 90 and 97; D = 72: 256 tokens 20 and
-// 15, 1024 tokens 36 and 39).
+// walk over the dropped keys, instead of as one kernel.  Both sides' times are compared in
+// steps of 64 keys of the dense walk.  The dense walk passes every block, so the two take n
+// steps, a share for each kept block of a row, and a constant for the second launch; the single
+// kernel takes n steps of `slower` times the length.  All three are fitted to 280 calls of
+// 1024 to 17776 tokens and 32 to 17000 waves, each timed with both (single against two,
+// us: D = 64, 32 heads of 2048 56.1 and 57.3; 8 heads 50.9 and 48.7; 31 of 8192 547 and 502;
+// D = 72, 60 heads of 1024 45.4 and 45.4; 17 of 4096 298 and 176).
+// Four waves to a workgroup, one to four of them with rows, may need one more round over the 256
+// CUs than single waves do: then that round decides (D = 64, 24 heads of 2600 two kernels
+// 0.77 times the speed, 26 heads 0.96; 17776 tokens, 11 heads 0.95, 14 heads 1.10).
 bool cache_in_two(const AttnArgs& a, int D) {
     if (a.T < (D == 64 ? 2048 : 1024)) return false;
-    const double blocks = (double)a.n_masks * a.n_blk * a.n_blk;
-    return a.nnz <= blocks / (D == 64 ? 8 : 3);
+    const int items = a.n_items, n = a.n_blk;
+    const double kept = (double)a.nnz / ((double)a.n_masks * n);
+    const int rounds1 = (items + 1023) / 1024;
+    const int rounds4 = (items / n * ((n + 3) / 4) + 255) / 256;
+    double slower, share, launch, extra = 0.0;
+    if (D == 64) {  // 1024 single waves are one to a SIMD, 2048 two
+        slower = items <= 768 ? 1.265 : items <= 1024 ? 1.20 : items <= 2048 ? 1.15 : 1.18;
+        share = 0.93;
+        launch = 6.5;
+        if (rounds4 > rounds1) extra = 0.65 / (rounds1 > 2 ? rounds1 : 2);
+    } else {  // the single kernel runs one wave to a SIMD, the dense walk two
+        slower = items <= 1024 ? 1.45 : 1.65;
+        share = 0.75;
+        launch = items <= 1024 ? 2.0 + items / 200.0 : 5.0;
+        if (rounds4 > rounds1 && rounds1 <= 2) extra = rounds1 == 1 ? 0.6 : 0.3;
+    }
+    return n * (1.0 + extra) + share * kept + launch < slower * n;
 }
 
 }  // namespace
