@@ -1136,7 +1136,7 @@ bool few_waves(const AttnArgs& a) {
     const int64_t blocks = a.dense ? a.n_blk : a.nnz / ((int64_t)a.n_masks * a.n_blk);  // kept by a row
     const bool uneven = a.n_items > 2048 && a.n_items <= 6144;
     if (a.row_max || a.row_sum) return uneven && blocks <= 2;
-    return uneven || a.n_items <= 512 || (a.n_items <= 1024 && blocks >= 16);
+    return uneven || a.n_items <= 512 || (a.n_items <= 1024 && blocks >= 15);
 }
 
 template <int D, int BS>
@@ -1169,6 +1169,11 @@ AttnArgs in_rows_of(AttnArgs a, int rows) {
     return a;
 }
 
+// Rounds over the chip of `items` waves, one to a SIMD, and of their workgroups in attn_dense:
+// four waves, one to each SIMD of a CU, for every four of a head's n blocks.
+int64_t wave_rounds(int64_t items) { return (items + 1023) / 1024; }
+int64_t group_rounds(int64_t items, int n) { return (items / n * ((n + 3) / 4) + 255) / 256; }
+
 // Dense attention: waves of 32 rows (attn_fwd), of 64 rows with a ring each (attn_rows64 or
 // attn_fwd), or four of 64 rows over a shared ring (attn_dense).
 //  - Up to 1024 waves of 32 rows (one per SIMD of the chip) a chunk's latency bounds the
@@ -1179,14 +1184,13 @@ AttnArgs in_rows_of(AttnArgs a, int rows) {
 //    tokens at D = 64 (800 heads 15.0, 18.3, 23.0), 96 at D = 72 (1000 heads 12.7, 14.2, 20.7),
 //    224 while two rounds hold all (D = 64, 600 heads: 19.4, 21.3, 23.0), and 448 while few
 //    SIMDs hold two (D = 72, 120 heads of 288: 10.3, 11.3, 12.8).
-//  - Up to 14 blocks of 64 a wave's own ring wins: of a workgroup of four the waves past
-//    the last row walk for nothing (D = 72: 4096 heads of 64 24.7 and 42.7; 512 of 320 28.6 and
-//    35.6; 300 of 832 73.6 and 88.8).  Where none is idle and there are many of them
-//    the shared ring does (D = 72: 1024 heads of 512 113 and 104; 1024 of 250 39.0 and 40.0, 4096
-//    147 and 136).
-//  - Longer walks take the shared ring (D = 72, 32 heads of 4096: own rings 166, shared 156)
-//    but for 64-wide heads without statistics at one wave per SIMD (16 heads of 4096: attn_fwd
-//    75.5, shared 76.7; 9 heads 70.2 and 72.6).
+//  - The shared ring takes 0.93 times the time of a ring each in walks of 15 and more
+//    blocks, or in many waves (D = 72: 32 heads of 4096 156 and 166; 1024 of 512 104 and 113, 256
+//    28.8 and 30.0), unless its workgroups, the idle waves past a head's last row among them,
+//    need more rounds over the 256 CUs than single waves do over the 1024 SIMDs (D = 72: 48
+//    heads of 2600 146 and 107; 45 98 and 103; 22 of 17776 2162 and 2041; 4096 of 64 42.7 and 24.7).
+//  - 64-wide heads without statistics at one wave per SIMD are faster alone (16 heads of
+//    4096: attn_fwd 75.5, shared 76.7; 9 heads 70.2 and 72.6).
 hipError_t launch_dense(const AttnArgs& a, int D, hipStream_t stream) {
     const AttnArgs a32 = in_rows_of(a, 32), a64 = in_rows_of(a, 64);
     const int waves = a32.n_items, blocks = a64.n_blk;
@@ -1195,7 +1199,8 @@ hipError_t launch_dense(const AttnArgs& a, int D, hipStream_t stream) {
         rows32 |= a.T <= (D == 64 ? 160 : 96) || (a.T <= 224 && waves <= 4608) || (a.T <= 448 && waves <= 1280);
     if (rows32) return D == 64 ? launch_db<64, 32>(a32, kAttn, stream) : launch_db<72, 32>(a32, kAttn, stream);
     const bool alone = D == 64 && !a.row_max && !a.row_sum && a64.n_items <= 1024;
-    if (blocks > 14 ? !alone : blocks % 4 == 0 && a64.n_items > 4096)
+    const int64_t rounds1 = wave_rounds(a64.n_items), rounds4 = group_rounds(a64.n_items, blocks);
+    if (!alone && (blocks > 14 || a64.n_items > 4096) && 100 * rounds4 <= 107 * rounds1)
         return launch_attention_dense(a, D, false, stream);
     if (D == 72) return launch_rows64<72>(a64, kAttn, stream);
     return blocks <= 3 ? launch_rows64<64>(a64, kAttn, stream) : launch_db<64, 64>(a64, kAttn, stream);
@@ -1216,14 +1221,13 @@ bool cache_in_two(const AttnArgs& a, int D) {
     if (a.T < (D == 64 ? 2048 : 1024)) return false;
     const int items = a.n_items, n = a.n_blk;
     const double kept = (double)a.nnz / ((double)a.n_masks * n);
-    const int rounds1 = (items + 1023) / 1024;
-    const int rounds4 = (items / n * ((n + 3) / 4) + 255) / 256;
+    const int64_t rounds1 = wave_rounds(items), rounds4 = group_rounds(items, n);
     double slower, share, launch, extra = 0.0;
     if (D == 64) {  // 1024 single waves are one to a SIMD, 2048 two
         slower = items <= 768 ? 1.265 : items <= 1024 ? 1.20 : items <= 2048 ? 1.15 : 1.18;
         share = 0.93;
         launch = 6.5;
-        if (rounds4 > rounds1) extra = 0.65 / (rounds1 > 2 ? rounds1 : 2);
+        if (rounds4 > rounds1) extra = 0.65 / (double)(rounds1 > 2 ? rounds1 : 2);
     } else {  // the single kernel runs one wave to a SIMD, the dense walk two
         slower = items <= 1024 ? 1.45 : 1.65;
         share = 0.75;

@@ -1,8 +1,8 @@
 """Dense attention at the lines where its kernel changes: heads of up to 896 tokens in waves of
 32 rows or of 64 with a ring each (an odd count of 32-row tiles, 96 / 160 / 224 / 448
 tokens, 1024 to 4608 waves), more than 896 tokens, or many heads of 4 blocks, in workgroups
-of four waves of which one to four hold rows, 64-wide heads without statistics at 1024 and
-1025 waves of 64 rows."""
+of four waves of which one to four hold rows, or in single waves where those workgroups
+need another round, 64-wide heads without statistics at 1024 and 1025 waves of 64 rows."""
 
 import numpy as np
 import pytest
@@ -19,7 +19,8 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(1100, 31), (1100, 32), (600, 33), (600, 64), (400, 65), (400, 96), (400, 97), (300, 128), (300, 129), (300, 160),
           (300, 161), (250, 192), (250, 193), (200, 224), (662, 224), (160, 250), (1024, 250), (1025, 250), (160, 288), (142, 288), (80, 480),
           (32, 1024), (48, 1024), (57, 850), (55, 896), (72, 896), (72, 897), (110, 320), (410, 320), (70, 960), (70, 961),
-          (64, 1024), (65, 1024), (62, 1025), (58, 1120), (55, 1180), (16, 4096), (205, 320), (205, 300)]
+          (64, 1024), (65, 1024), (62, 1025), (58, 1120), (55, 1180), (16, 4096), (205, 320), (205, 300),
+          (64, 1088), (60, 1088), (115, 1088), (125, 1088), (46, 1400)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
