@@ -23,8 +23,9 @@
 //                  [D / 4][blocks of the tile][4], the order a wave reads it in.
 //                  Bound by HBM: CogVideoX shape 43 us for 273 MB.
 //   select_kernel  one workgroup per (batch, head) and a few query blocks, a wave per
-//                  tile of 64 key blocks (up to 8 waves) and two rows per wave while the
-//                  scores fit 40 KB of LDS.  A lane keeps its key block's mean in
+//                  tile of 64 key blocks (up to 8 waves) and two rows per wave (one where
+//                  a row has more than 512 blocks) while the scores fit 40 KB of
+//                  LDS.  A lane keeps its key block's mean in
 //                  registers and takes the query values from scalar registers, so
 //                  that a term of a score is one vector instruction and no LDS read.
 //                  Then one wave per row selects: up to 512 blocks with the keys in
@@ -341,10 +342,12 @@ hipError_t launch_dynamic_index(const DynIndexArgs& a, hipStream_t stream) {
                        a.block, a.n_blk, a.qsum, a.kmean);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // a wave per 64 key blocks and two rows per wave, while their scores fit
+    // A wave per 64 key blocks and, while their scores fit, two rows per wave; one where radix
+    // passes select, whose latency two rows in turn double (556 blocks, D = 64, 1 head:
+    // 20.6 us, two rows 35.6; 60 heads 161 and 169).
     const int n_tile = (a.n_blk + 63) / 64;
     const int waves = n_tile < kSelWaves ? n_tile : kSelWaves;
-    int rows = 2 * waves;
+    int rows = (n_tile > kSelRegs ? 1 : 2) * waves;
     const int fit = (int)(kSelScoreBytes / (a.n_blk * sizeof(float)));  // >= 2: n_blk <= 4096
     if (rows > fit) rows = fit;
     const int n_grp = (a.n_blk + rows - 1) / rows;
