@@ -362,12 +362,18 @@ hipError_t launch_dynamic_index(const DynIndexArgs& a, hipStream_t stream) {
             hipLaunchKernelGGL((select_kernel<72, N>), grid, block, lds, stream, a.qsum, a.kmean, a.n_blk, a.keep, rows,
                                a.row_ptr, a.col_idx);
     };
-    if (n_tile <= 1) go(std::integral_constant<int, 1>{});
-    else if (n_tile <= 2) go(std::integral_constant<int, 2>{});
-    else if (n_tile <= 4) go(std::integral_constant<int, 4>{});
-    else if (n_tile <= 5) go(std::integral_constant<int, 5>{});
-    else if (n_tile <= kSelRegs) go(std::integral_constant<int, kSelRegs>{});
-    else go(std::integral_constant<int, 0>{});
+    static_assert(kSelRegs == 8, "one case for each count of tiles");
+    switch (n_tile) {  // a row's keys take as many registers as it has tiles
+        case 1: go(std::integral_constant<int, 1>{}); break;
+        case 2: go(std::integral_constant<int, 2>{}); break;
+        case 3: go(std::integral_constant<int, 3>{}); break;
+        case 4: go(std::integral_constant<int, 4>{}); break;
+        case 5: go(std::integral_constant<int, 5>{}); break;
+        case 6: go(std::integral_constant<int, 6>{}); break;
+        case 7: go(std::integral_constant<int, 7>{}); break;
+        case 8: go(std::integral_constant<int, 8>{}); break;
+        default: go(std::integral_constant<int, 0>{});
+    }
     return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
 """The selection of the dynamic mask at the sizes where its kernels change: every count of
-64-block tiles a row is selected with in registers (1, 2, 4, 5, 8) and one block more, the
-radix passes above 512 blocks, and the fewest rows a workgroup takes.  Inputs are
+64-block tiles a row is selected with in registers (1 to 8), the radix passes above 512
+blocks, and the fewest rows a workgroup takes.  Inputs are
 small integers, so that every score is exact and many are equal."""
 
 import numpy as np
@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("D", [64, 72])
-@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 256, 257, 320, 321, 512, 513, 1300])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 256, 257, 320, 321, 448, 512, 513, 1300])
 def test_selection_at_tile_counts(gpu, D, n):
     B, H, block = 1, 2, 32
     T = n * block
