@@ -72,6 +72,7 @@ constexpr int kWaves = (D == 72 && BS == 64) ? 1 : 2;
 template <int D, int BS, bool RESHAPE, bool STATS, bool CACHE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves<D, BS>)))
 void attn_fwd(AttnArgs a) {
+    static_assert(BS == 32 || D == 64 || CACHE, "72-wide heads walk 64-token blocks in attn_rows64");
     using G = Geo<D>;
     constexpr int DK = G::DK;
     constexpr int DV = G::DV;
@@ -852,6 +853,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     constexpr int HALF = 32 * ROWB;          // one 32-key chunk, one ring stage
     constexpr int NDMA = (HALF + 1023) / 1024;  // DMA instructions per chunk and tensor
     constexpr bool TAIL = D == 72;
+    const bool dense = !RESHAPE && a.dense;  // every block of the head, no CSR
     // K stages at 0 and HALF, V stages at 2 HALF and 3 HALF, zeros for the tails' operands
     constexpr int ZERO = 4 * HALF;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[ZERO + (TAIL ? 8 * ROWB + 16 : 0)];
@@ -887,7 +889,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 
     // ---- kept key blocks of this query block ----------------------------------------
     int e_beg, e_end;
-    if (a.dense) {
+    if (dense) {
         e_beg = 0;
         e_end = a.n_blk;
     } else {
@@ -903,7 +905,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     // one VGPR (lane j holds entry e_beg + j); longer rows read the rest with loads.
     const int n = (e_end - e_beg) * 2;
     int cols = -1;
-    if (!a.dense && lane < e_end - e_beg) cols = a.col_idx[e_beg + lane];
+    if (!dense && lane < e_end - e_beg) cols = a.col_idx[e_beg + lane];
     // A chunk is addressed by the byte offset of its first key row in the head's K (or V)
     // buffer, or kOob for a chunk that holds no key (past the row, past T, an entry
     // outside [0, n_blk)): its loads read zeros and its scores are masked.
@@ -914,7 +916,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     // The first chunks' entries come by scalar loads: vector loads return in order, and
     // `cols` behind Q, whose HBM latency the first K and V loads are not to wait for.
     int kb0 = 0, kb1 = 1;
-    if (!a.dense && n > 0) {
+    if (!dense && n > 0) {
         kb0 = ((csr_ptr)a.col_idx)[e_beg];
         kb1 = n > 2 ? ((csr_ptr)a.col_idx)[e_beg + 1] : -1;
     }
@@ -927,7 +929,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         const int i = c0 + lane;
         const int j = i >> 1;
         int kb = j;
-        if (!a.dense) {
+        if (!dense) {
             const int last = (c0 + 63 < n ? c0 + 63 : n - 1) >> 1;
             if (last < 64) {  // every entry this table needs sits in `cols`
                 kb = __builtin_amdgcn_ds_bpermute((j & 63) << 2, cols);

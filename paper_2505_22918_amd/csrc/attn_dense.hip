@@ -6,7 +6,7 @@
 //                  keys' statistics, the other keys, then O_full, rho (Eq.8), R (Eq.10)
 //
 // Every query block of a head reads the whole K and V of that head, so a
-// workgroup of W waves (64 query rows each, two waves per SIMD) shares one K and one V
+// workgroup of four waves (64 query rows each, two waves per SIMD) shares one K and one V
 // ring in LDS, three 64-key stages each, filled by all its waves with
 // buffer_load ... lds; one barrier per 64 keys, two stages of lead.  With a ring
 // per wave the chunk loads kept the vector-memory path 84-92 % busy.
@@ -34,8 +34,9 @@ constexpr int kOff = 0x60000000;  // buffer offset past every record, also after
 constexpr int kAct = 1;           // flags in the low bits of a block offset: this wave scores the block
 constexpr int kEnd = 2;           // past the last block
 constexpr int kFlags = 3;
+constexpr int W = 4;              // waves of a workgroup: one to each SIMD of a CU
 
-template <int D, int W, bool STATS, bool CACHE>
+template <int D, bool STATS, bool CACHE>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_dense(AttnArgs a) {
     using G = Geo<D>;
     constexpr int ROWB = G::SLOTS * 16;      // LDS bytes per K / V row (= 2 * D)
@@ -59,8 +60,6 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l32 = lane & 31;
-    const int hi = lane >> 5;
 
     const int g = blockIdx.x;
     const int item = (g & 7) * a.per_xcd + (g >> 3);
@@ -309,27 +308,27 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     }
 }
 
-template <int D, int W, bool STATS, bool CACHE>
+template <int D, bool STATS, bool CACHE>
 hipError_t launch_one(AttnArgs a, hipStream_t stream) {
     const int64_t n64 = ((int64_t)a.T + 63) / 64;
     const int64_t n_bh = a.n_items / a.n_blk;
     a.n_items = (int32_t)(n_bh * ((n64 + W - 1) / W));
     a.per_xcd = (a.n_items + 7) / 8;
-    hipLaunchKernelGGL((attn_dense<D, W, STATS, CACHE>), dim3(8 * a.per_xcd), dim3(64 * W), 0, stream, a);
+    hipLaunchKernelGGL((attn_dense<D, STATS, CACHE>), dim3(8 * a.per_xcd), dim3(64 * W), 0, stream, a);
     return hipGetLastError();
 }
 
-template <int D, int W>
-hipError_t launch_dw(const AttnArgs& a, bool cache, hipStream_t stream) {
+template <int D>
+hipError_t launch_d(const AttnArgs& a, bool cache, hipStream_t stream) {
     const bool stats = a.row_max != nullptr || a.row_sum != nullptr;
-    if (cache) return stats ? launch_one<D, W, true, true>(a, stream) : launch_one<D, W, false, true>(a, stream);
-    return stats ? launch_one<D, W, true, false>(a, stream) : launch_one<D, W, false, false>(a, stream);
+    if (cache) return stats ? launch_one<D, true, true>(a, stream) : launch_one<D, false, true>(a, stream);
+    return stats ? launch_one<D, true, false>(a, stream) : launch_one<D, false, false>(a, stream);
 }
 
 }  // namespace
 
 hipError_t launch_attention_dense(const AttnArgs& a, int D, bool cache, hipStream_t stream) {
-    return D == 64 ? launch_dw<64, 4>(a, cache, stream) : launch_dw<72, 4>(a, cache, stream);
+    return D == 64 ? launch_d<64>(a, cache, stream) : launch_d<72>(a, cache, stream);
 }
 
 }  // namespace rt

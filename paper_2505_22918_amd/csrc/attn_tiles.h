@@ -63,7 +63,6 @@ struct Tiles {
     using G = Geo<D>;
     static constexpr int DS = 4;                // 16-wide k-steps of Q K^T (and a tail step)
     static constexpr int ROWB = G::SLOTS * 16;  // LDS bytes per K / V row (= 2 * D)
-    static constexpr int HALF = 32 * ROWB;      // one 32-key chunk
     static constexpr bool TAIL = D == 72;       // 8 head dims past the two 32-row tiles of O^T
     static_assert(ROWB == 2 * D, "rows are unpadded");
 

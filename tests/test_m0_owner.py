@@ -79,8 +79,8 @@ def check_m0(insts, src):
 def test_m0_is_written_only_by_the_dma_blocks(tmp_path, src):
     insts = _instructions(_device_asm(src, str(tmp_path / (src + ".s"))))
     n_blocks = check_m0(insts, src)
-    if src == "attn.hip":
-        assert n_blocks > 0  # the check saw the DMA blocks it guards
+    # the check saw the DMA blocks it guards
+    assert (n_blocks > 0) == (src in ("attn.hip", "attn_dense.hip"))
 
 
 GOOD = """s_mov_b32 m0, s12
