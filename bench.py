@@ -22,6 +22,7 @@ import hashlib
 import json
 import math
 import os
+import re
 import sys
 import time
 
@@ -82,12 +83,16 @@ def _code_only(text):
 
 
 def kernel_source_sha256():
-    """Digest of the attention kernel's code (comments and layout ignored); a
-    counter summary applies only to the kernel it was taken from."""
-    h = hashlib.sha256()
-    for name in ("attn.hip", "kernels.h"):
-        with open(os.path.join(ROOT, "paper_2505_22918_amd", "csrc", name), encoding="utf-8") as f:
-            h.update(_code_only(f.read()).encode())
+    """Digest of the fused kernel's code, attn.hip and every header it includes
+    (comments and layout ignored); a counter summary applies only to the kernel
+    it was taken from."""
+    csrc = os.path.join(ROOT, "paper_2505_22918_amd", "csrc")
+    names, h = ["attn.hip"], hashlib.sha256()
+    for name in names:  # grows by what each file includes
+        with open(os.path.join(csrc, name), encoding="utf-8") as f:
+            code = f.read()
+        names += [n for n in re.findall(r'^\s*#include "([^"]+)"', code, re.M) if n not in names]
+        h.update(_code_only(code).encode())
     return h.hexdigest()
 
 

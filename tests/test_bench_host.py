@@ -46,13 +46,17 @@ def test_traffic_line_matches_only_its_kernel(tmp_path, monkeypatch):
         f"bench-traffic: workload={wl} kernel_sha256={bench.kernel_source_sha256()} fetch_bytes=10 write_bytes=5\n")
     monkeypatch.setattr(bench, "ROOT", str(tmp_path))
     os.makedirs(tmp_path / "paper_2505_22918_amd" / "csrc")
-    for name in ("attn.hip", "kernels.h"):
+    # the kernel's code: attn.hip, the launch arguments, and the walk and its building blocks
+    csrc = tmp_path / "paper_2505_22918_amd" / "csrc"
+    names = ("attn.hip", "kernels.h", "attn_tiles.h", "attn_common.h")
+    for name in names:
         with open(os.path.join(os.path.dirname(bench.__file__), "paper_2505_22918_amd", "csrc", name)) as f:
-            (tmp_path / "paper_2505_22918_amd" / "csrc" / name).write_text(f.read())
+            (csrc / name).write_text(f.read())
     assert bench.measured_traffic(wl) == 15
-    with open(tmp_path / "paper_2505_22918_amd" / "csrc" / "attn.hip", "a") as f:
-        f.write("\n// a comment changes nothing\n")
-    assert bench.measured_traffic(wl) == 15
-    with open(tmp_path / "paper_2505_22918_amd" / "csrc" / "attn.hip", "a") as f:
-        f.write("\nstatic int changed_code;\n")
-    assert bench.measured_traffic(wl) is None
+    for name in names:
+        code = (csrc / name).read_text()
+        (csrc / name).write_text(code + "\n// a comment changes nothing\n")
+        assert bench.measured_traffic(wl) == 15, name
+        (csrc / name).write_text(code + "\nstatic int changed_code;\n")
+        assert bench.measured_traffic(wl) is None, name
+        (csrc / name).write_text(code)
