@@ -1,4 +1,5 @@
-"""CPU model of the attention kernel's addressing and load/wait schedule.
+"""CPU model of attn_fwd's addressing and load/wait schedule (the two-tile kernels have
+theirs in kernel_model_tiles.py).
 
 Test infrastructure.  It restates, in plain Python, the index arithmetic of
 attn_fwd in paper_2505_22918_amd/csrc/attn.hip (per-lane DMA and LDS offsets,

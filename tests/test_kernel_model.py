@@ -1,4 +1,6 @@
-"""The CPU model of the attention kernel (tests/kernel_model.py): every global
+"""The CPU model of attn_fwd (tests/kernel_model.py), over every shape it is compiled
+for and 72-wide heads over 64-token blocks as well (calls that go to the two-tile kernels,
+test_kernel_model_tiles.py, by their size or width included): every global
 and LDS address stays in bounds for every distinct work item of the five
 workloads (each query block, at the first and the last head) and for every
 item of seeded random launches with shared, per-head and per-(batch, head)
