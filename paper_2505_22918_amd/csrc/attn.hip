@@ -1042,11 +1042,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         if (STATS) t.m_top[qt] = pair_max(t.m_top[qt]);
         if (STATS && hi == 0 && row < T) {
             const size_t si = ((size_t)bh * T + row) * a.stat_stride;
-            // before the second half of a caching step (rows D / 2 floats apart) the sum is
-            // against a finite max: a row that kept no key leaves 0, not 0 * exp2(inf)
-            const float ref = a.stat_stride == 1 ? t.m_top[qt] : fmaxf(t.m_top[qt], -1e30f);
-            if (a.row_max) a.row_max[si] = t.m_top[qt] * a.scale_nat;
-            if (a.row_sum) a.row_sum[si] = l_tot * __builtin_amdgcn_exp2f((t.m_run[qt] - ref) * a.scale_log2);
+            if (a.stat_stride != 1) {  // for the second half of a caching step: the running pair
+                a.row_max[si] = t.m_run[qt];
+                a.row_sum[si] = l_tot;
+            } else {
+                if (a.row_max) a.row_max[si] = t.m_top[qt] * a.scale_nat;
+                if (a.row_sum)
+                    a.row_sum[si] = l_tot * __builtin_amdgcn_exp2f((t.m_run[qt] - t.m_top[qt]) * a.scale_log2);
+            }
         }
         const lds_u8* Rs = lds + ((n + qt) & 1) * HALF;  // residual rows: the K stage of chunk n + qt
 #pragma unroll
@@ -1244,11 +1247,10 @@ bool cache_in_two(const AttnArgs& a, int D) {
 hipError_t launch_attention(const AttnArgs& a, int D, int block, AttnMode mode, hipStream_t stream) {
     if (mode == kAttn && a.dense) return launch_dense(a, D, stream);
     if (mode == kAttnCache && block == 64 && !a.postmask && cache_in_two(a, D)) {
-        AttnArgs s = a;  // O_s to o, the kept keys' statistics to the residual rows
+        AttnArgs s = a;  // O_s to o, the kept keys' running max and sum to the residual rows
         s.row_max = reinterpret_cast<float*>(a.resid_out);
         s.row_sum = s.row_max + 1;
         s.stat_stride = D / 2;
-        s.scale_nat = 1.0f;
         const hipError_t e = D == 64 ? launch_rows64<64>(s, kAttn, stream) : launch_rows64<72>(s, kAttn, stream);
         return e != hipSuccess ? e : launch_attention_dense(a, D, true, stream);
     }

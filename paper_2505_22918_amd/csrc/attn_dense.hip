@@ -163,21 +163,17 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     t.settle_q();  // issued first
     barrier();
     t.first_chunk(2 * PAIR + HALF, b0 & ~kFlags);
-    // Both tiles start from their first chunk's max.  A caching step starts from the max
-    // m of the kept keys (-inf where none has a score above it), which the sparse walk
-    // before it left with their exp-sum against max(m, -1e30) in the first 8 bytes of the
-    // residual row.
+    // Both tiles start from their first chunk's max.  A caching step goes on from the running
+    // max of the sparse walk before it, which left it with the kept keys' exp-sum against it
+    // in the first 8 bytes of the residual row: the probabilities round as in one walk.
     const bool has_in = CACHE && n_kept > 0;
     auto kept_stat = [&](int qt, int i) {
         const int row = row0 + qt * 32 + t.l32;
         return row < T ? reinterpret_cast<const float*>(a.resid_out + head_off + (size_t)row * D)[i] : 0.f;
     };
     if (has_in) {
-#pragma unroll
-        for (int qt = 0; qt < 2; ++qt) {
-            t.m_top[qt] = kept_stat(qt, 0);
-            t.m_run[qt] = fmaxf(t.m_top[qt], -1e30f);
-        }
+        t.m_run[0] = kept_stat(0, 0);
+        t.m_run[1] = kept_stat(1, 0);
     } else {
         t.first_max(2 * PAIR + HALF, b0 & ~kFlags);
     }
@@ -244,10 +240,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         const int row = row0 + qt * 32 + t.l32;
         const float ls = pair_sum(t.l_run[qt]);
         float li = 0.f;
-        if (has_in) {
-            const float m = fmaxf(kept_stat(qt, 0), -1e30f);
-            li = kept_stat(qt, 1) * __builtin_amdgcn_exp2f((m - t.m_run[qt]) * a.scale_log2);
-        }
+        if (has_in) li = kept_stat(qt, 1) * __builtin_amdgcn_exp2f((kept_stat(qt, 0) - t.m_run[qt]) * a.scale_log2);
         const float lf = CACHE ? li + ls : ls;
         const float inv = 1.0f / lf;
         const float rho = split ? li / lf : 1.0f;  // exactly 1 when every block is kept

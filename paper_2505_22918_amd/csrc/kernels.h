@@ -14,7 +14,7 @@ struct AttnArgs {
     uint16_t* o;        // bf16 [B,H,T,D]
     float* row_max;     // fp32 [B,H,T] or null
     float* row_sum;     // fp32 [B,H,T] or null
-    int32_t stat_stride;  // floats from one row's row_max / row_sum to the next's (1 for the caller's)
+    int32_t stat_stride;  // 1, or (caching step, first half) floats from one row's running max and sum to the next's
     const float* rho;   // reshape only: fp32 [B,H,T]
     const uint16_t* resid;  // reshape only: bf16 [B,H,T,D]
     float rho_delta;
@@ -44,8 +44,9 @@ hipError_t launch_attention(const AttnArgs& a, int D, int block, AttnMode mode, 
 
 // The walks over every key block (attn_dense.hip), called by launch_attention:
 // dense attention, or (cache) the second half of a caching step over 64-token
-// blocks: o holds O_s and the first 8 bytes of each resid_out row the kept keys'
-// largest unscaled score m and their exp-sum against max(m, -1e30).
+// blocks: o holds O_s and the first 8 bytes of each resid_out row the running
+// max (an unscaled score, finite) that the kept keys' walk ended with and their
+// exp-sum against it.
 hipError_t launch_attention_dense(const AttnArgs& a, int D, bool cache, hipStream_t stream);
 
 hipError_t launch_cache_build(const uint16_t* o_full, const float* m_full, const float* l_full,
