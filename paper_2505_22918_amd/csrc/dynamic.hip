@@ -234,11 +234,13 @@ __device__ __forceinline__ Cut cut_by_radix(const float* row, int n_blk, int qb,
     return {thr, rem};
 }
 
-// N: 64-block tiles of a row selected in registers, 0 for any number by radix passes
+// N: 64-block tiles of a row selected in registers, 0 for any number by radix passes.
+// n_wave, the waves of the workgroup, is an argument: blockDim would bring the hidden
+// kernel arguments in, whose filling costs the host 0.4 us a launch.
 template <int D, int N>
 __global__ __launch_bounds__(64 * kSelWaves) void select_kernel(const float* __restrict__ qsum,
                                                                 const float* __restrict__ kmean, int n_blk, int keep,
-                                                                int rows, int32_t* __restrict__ row_ptr,
+                                                                int rows, int n_wave, int32_t* __restrict__ row_ptr,
                                                                 int32_t* __restrict__ col_idx) {
     // scores of the workgroup's rows: rows x n_blk floats, then (radix) the waves' histograms
     extern __shared__ float sc[];
@@ -248,7 +250,6 @@ __global__ __launch_bounds__(64 * kSelWaves) void select_kernel(const float* __r
     const int n_row = n_blk - qb0 < rows ? n_blk - qb0 : rows;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n_wave = blockDim.x >> 6;
     const int kk = keep < n_blk ? keep : n_blk;
     const int need = kk - 1;  // other blocks to keep, < n_blk
     const float* kh = kmean + (size_t)bh * n_blk * D;
@@ -357,10 +358,10 @@ hipError_t launch_dynamic_index(const DynIndexArgs& a, hipStream_t stream) {
         constexpr int N = decltype(tiles)::value;
         if (a.D == 64)
             hipLaunchKernelGGL((select_kernel<64, N>), grid, block, lds, stream, a.qsum, a.kmean, a.n_blk, a.keep, rows,
-                               a.row_ptr, a.col_idx);
+                               waves, a.row_ptr, a.col_idx);
         else
             hipLaunchKernelGGL((select_kernel<72, N>), grid, block, lds, stream, a.qsum, a.kmean, a.n_blk, a.keep, rows,
-                               a.row_ptr, a.col_idx);
+                               waves, a.row_ptr, a.col_idx);
     };
     static_assert(kSelRegs == 8, "one case for each count of tiles");
     switch (n_tile) {  // a row's keys take as many registers as it has tiles
