@@ -1129,19 +1129,20 @@ hipError_t launch_one(const AttnArgs& a, hipStream_t stream) {
 
 // Whether a walk of 64-wide heads over 64-token blocks is faster as attn_fwd than as
 // attn_rows64.  The chip holds 1024 such waves one to a SIMD and 2048 two to a SIMD.  A
-// wave that is alone, or among rounds that fill unevenly, gains nothing from
-// attn_rows64's interleaving and pays for its two half steps (attn_fwd against
-// attn_rows64: 256 items of 16 kept blocks 19.3 us and 20.6, fused 20.7 and 21.3; 1024 of 32
-// 41.2 and 42.3; 3072 of 4 25.1 and 25.8, fused 27.2 and 28.2); from four rounds
-// on, and where one round puts two waves on some SIMDs, it is the faster (16680
-// of 9 fused 226 and 221; 1280 of 4 13.6 and 13.0).  With statistics, which
-// attn_fwd pays more for, only rows of one or two blocks in uneven rounds are faster there
-// (3840 of 2: 24.4 and 25.4; of 8: 49.6 and 48.2).
+// wave that is alone, or among rounds that fill unevenly, gains little from
+// attn_rows64's interleaving and pays for its two half steps; from four rounds on, and where
+// some SIMDs hold two waves and others one, attn_rows64 is the faster.  Measured, attn_fwd
+// against attn_rows64, us: 256 items of 16 kept blocks 19.3 and 20.6, fused 20.7 and 21.3;
+// 1024 of 32 41.2 and 42.3, of 4 10.0 and 9.4; 1280 of 4 13.6 and 13.0; 1792 of 2 12.6 and 13.5,
+// fused 13.8 and 14.2; 3072 of 4 25.1 and 25.8, fused 27.2 and 28.2; 16680 of 9 fused 226 and
+// 221.  With statistics, which attn_fwd pays more for, only short rows in uneven rounds
+// are faster there (3840 of 2: 24.4 and 25.4; of 8: 49.6 and 48.2).
 bool few_waves(const AttnArgs& a) {
     const int64_t blocks = a.dense ? a.n_blk : a.nnz / ((int64_t)a.n_masks * a.n_blk);  // kept by a row
-    const bool uneven = a.n_items > 2048 && a.n_items <= 6144;
-    if (a.row_max || a.row_sum) return uneven && blocks <= 2;
-    return uneven || a.n_items <= 512 || (a.n_items <= 1024 && blocks >= 15);
+    const bool uneven = a.n_items > 1408 && a.n_items <= 6144;
+    if (a.row_max || a.row_sum) return uneven && blocks <= 3;
+    if (uneven) return a.n_items > 2048 || blocks <= 8;
+    return a.n_items <= 512 || (a.n_items <= 1024 && blocks >= 15);
 }
 
 template <int D, int BS>

@@ -1,6 +1,7 @@
 """64-wide heads over 64-token blocks on both sides of the rule that gives few waves attn_fwd
-and others attn_rows64: 512 and 513 waves, 1024 with 14 and 15 kept blocks a row, 2048 and
-2049, 6144 and 6145 (with statistics: rows of 2 and 3 blocks), and the walk's edges with
+and others attn_rows64: 512 and 513 waves, 1024 with 14 and 15 kept blocks a row, 1408 and
+1409, 2048 with 8 and 9, 2049, 6144 and 6145 (with statistics: rows of 3 and 4 blocks), and
+the walk's edges with
 enough waves for attn_rows64 (rows of 1 to 3 blocks, of 31 to 34 and 64 to 66, last blocks of
 1, 32, 33 and 63 tokens)."""
 
@@ -60,8 +61,9 @@ def _mask(n, keep):
     return hm
 
 
-@pytest.mark.parametrize("H,n,keep", [(32, 16, 2), (27, 19, 2), (32, 32, 14), (32, 32, 15), (64, 32, 3), (683, 3, 2),
-                                      (683, 3, 3), (192, 32, 2), (192, 32, 3), (1229, 5, 2)])
+@pytest.mark.parametrize("H,n,keep", [(32, 16, 2), (27, 19, 2), (32, 32, 14), (32, 32, 15), (88, 16, 3), (1409, 1, 1),
+                                      (128, 11, 3), (64, 32, 8), (64, 32, 9), (683, 3, 3), (192, 32, 3), (192, 32, 4),
+                                      (1229, 5, 2)])
 @pytest.mark.parametrize("mode", ["sparse", "sparse stats", "reshape", "reshape stats"])
 def test_both_sides_of_the_rule(gpu, H, n, keep, mode):
     _check(H, 64 * n - 7, _mask(n, keep), mode)
