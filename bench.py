@@ -492,7 +492,8 @@ def main():
         "frac": (gbs / PEAK_HBM_GBS) if bound == "hbm" else (tflops / PEAK_BF16_TFLOPS),
         "traffic": traffic,
         "traffic_over_algorithmic": (traffic / nbytes) if traffic else None,
-        "kernel": (f"attn_rows64<{wl.D},reshape=true,stats=false>" if wl.block == 64
+        "kernel": (f"attn_rows64<{wl.D},reshape=true,stats=false>"
+                   if wl.block == 64 and (wl.D == 72 or wl.B * wl.H * wl.n_blk > 6144)
                    else f"attn_fwd<{wl.D},{wl.block},reshape=true,stats=false,cache=false>"),
         "algorithmic_bytes": nbytes,
         "algorithmic_flops": flops,
