@@ -37,7 +37,7 @@
 //                  keeps exactly min(keep, n_blk)).
 // Bound by the latency of the scalar loads and the L2 reads of the key means.  CogVideoX
 // shape (60 heads, 278 blocks, keep 9), before -> now: selection 65 -> 35 us (10 of them
-// the selection proper), the build 102-109 -> 85 us; one and four rows per wave 37 and
+// the selection proper), the build 102-109 -> 84 us; one and four rows per wave 37 and
 // 41 us; key means read row by row instead of by tiles 40 us.
 
 #include <hip/hip_runtime.h>
