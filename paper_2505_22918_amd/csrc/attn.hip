@@ -842,9 +842,9 @@ void attn_fwd(AttnArgs a) {
 // call takes 201, 216 and 211 us instead of 226, with all three 173.  Delaying
 // half of the first waves, wave priorities and an earlier K(0) change nothing.
 // Measured, fused call, attn_fwd -> this kernel: PixArt-Sigma-2K (32 heads, 16384 tokens,
-// D = 72) 161 -> 129 us (two waves per SIMD instead of one, rows stored from LDS),
+// D = 72) 163 -> 131 us (two waves per SIMD instead of one, rows stored from LDS),
 // PixArt-Sigma-1024 22.1 -> 19.1 us, CogVideoX (60 heads, 17776 tokens, D = 64)
-// 227 -> 221 us (the first step forms no P V and the last no scores: 4 % fewer MFMAs).
+// 229 -> 223 us (the first step forms no P V and the last no scores: 4 % fewer MFMAs).
 template <int D, bool RESHAPE, bool STATS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_rows64(AttnArgs a) {
     using G = Geo<D>;

@@ -17,9 +17,9 @@
 // beside its own; 131 instructions per 32-key chunk and 64 rows) and by power:
 // with zero queries, keys and values the same instructions run 21 % faster, as a
 // large bf16 product does.  Measured, before -> now: PixArt-Sigma-2K dense with
-// statistics (32 heads, 16384 tokens, D = 72) 3938 -> 2396 us (1.0 PFLOP/s of real
-// dims), CogVideoX caching step (60 heads, 17776 tokens, D = 64) 5442 -> 4831 us, of
-// which the sparse walk is 225; PixArt-Sigma-1024 caching step 290 -> 184 us.
+// statistics (32 heads, 16384 tokens, D = 72) 3925 -> 2534 us (0.98 PFLOP/s of real
+// dims), CogVideoX caching step (60 heads, 17776 tokens, D = 64) 5511 -> 4918 us, of
+// which the sparse walk is 225; PixArt-Sigma-1024 caching step 289 -> 192 us.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
